@@ -14,8 +14,8 @@
  *
  * Supported shapes: d in {64, 128}; block_k = 64; block_q in {64, 128};
  * N >= 1 with ragged last blocks (a block's statistics use only its valid
- * tokens); bf16 inputs (the hot path) and f32 inputs (a correctness-first
- * path).  The per-block routing lists live on chip, which bounds N: bf16 at
+ * tokens); bf16 inputs (the hot path) and f32 inputs (f32 products
+ * and sums throughout, on the f32 matrix instructions).  The per-block routing lists live on chip, which bounds N: bf16 at
  * d = 128 up to 1,478,656 tokens (1,048,576 with a causal mask), at d = 64 up
  * to 1,971,200 (1,015,808 causal); beyond that the forward returns
  * SOL_ERR_UNSUPPORTED.  Two workgroups share a compute unit up to 245,760

@@ -31,6 +31,23 @@ struct Shape {
 Shape make_shape(int B, int H, int N, int d, int bq, int bk, int mode, int dtype, int keep_tail_tokens,
                  int causal_granule = 0);
 
+// How the f32 attention kernel's workgroups share the query blocks: the first nb1 blocks (a multiple of 8, maybe
+// past the last block) are dealt to ns1 workgroups each, the others to ns2.  Every share of a block but the
+// first has a partial-output slot.
+struct F32Units {
+    int nb1 = 0, ns1 = 1, ns2 = 1;
+    int units(int blocks) const { return blocks <= nb1 ? blocks * ns1 : nb1 * ns1 + (blocks - nb1) * ns2; }
+    int grid(int blocks) const { return units((blocks + 7) / 8 * 8); }
+    size_t slots(int blocks) const { return (size_t)(units(blocks) - blocks); }
+    // partial outputs, then every workgroup's (max, row sum) pairs; a multiple of 256
+    size_t bytes(int blocks, int bq, int d) const {
+        return slots(blocks) ? slots(blocks) * bq * d * 4 + (size_t)units(blocks) * bq * 8 : 0;
+    }
+};
+// The whole workspace stays within kSplitRoom when partial outputs are part of it: that is the size of the
+// built-in scratch of the entry point that allocates nothing, so every entry point shares alike.
+constexpr size_t kSplitRoom = (size_t)64 << 20;
+
 // Workspace carve-up (all device pointers, 256-byte aligned inside one buffer).
 struct Workspace {
     float* qbar = nullptr;       // [BH][NQ][d]
@@ -47,6 +64,9 @@ struct Workspace {
     double* mom = nullptr;       // partial moments, moments_scratch_bytes()
     uint32_t* blkcount = nullptr;// [BH][NQ]
     uint32_t* queue = nullptr;   // [8][32] per-XCD claim counters of the bf16 attention kernel (one per 128 B)
+    float* part = nullptr;       // [slot][bq][d] partial outputs of shared query blocks (f32 path)
+    float* part_ml = nullptr;    // [workgroup][bq][2] running maxima and row sums
+    F32Units units;
 };
 
 // Returns the byte size; fills *ws when base != nullptr.

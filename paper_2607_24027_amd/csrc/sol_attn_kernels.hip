@@ -136,6 +136,24 @@ __global__ __launch_bounds__(256) void pool_mean_kernel(const T* __restrict__ x,
     pool_mean_block<T>(x, mean, N, D, blk, nb, blockIdx.x, blockIdx.y);
 }
 
+// The f32 forward's pooling in one launch: grid (NQ + NK [+ NK], BH), the query blocks, then the key
+// blocks, then (sparse mode) the value blocks; it also clears the head's count of selected pairs.
+__global__ __launch_bounds__(256) void prep_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
+                                                       const float* __restrict__ v, float* __restrict__ qbar,
+                                                       float* __restrict__ kbar, float* __restrict__ vbar,
+                                                       uint32_t* __restrict__ counts, int N, int D, int bq, int NQ,
+                                                       int NK) {
+    const int bh = blockIdx.y;
+    int j = blockIdx.x;
+    if (j == 0 && threadIdx.x == 0) counts[bh] = 0u;
+    const bool isq = j < NQ;
+    if (!isq) j -= NQ;
+    const bool isv = !isq && j >= NK;
+    if (isv) j -= NK;
+    pool_mean_block<float>(isq ? q : isv ? v : k, isq ? qbar : isv ? vbar : kbar, N, D, isq ? bq : kBlockK,
+                           isq ? NQ : NK, j, bh);
+}
+
 // ---------------------------------------------------------------------------
 // K/V preparation for the bf16 forward.  grid (NJ, BH), 256 threads, one key block each.
 //   vt     [BH][NK][D][64] f16: V^T tile by tile (each key block's transposed values are
@@ -449,12 +467,12 @@ __global__ __launch_bounds__(256) void tau_kernel(const float* __restrict__ qbar
 // receives the number of unselected routable blocks and *nsel of selected ones.
 //
 // The routable blocks are [0, nr) and the forced ones [nr, ne): without a causal mask
-// nr = NKr and ne = NK (the forced tail).  With a causal mask (CAUSAL) [0, nr) are the key
-// blocks every row of the query block sees and [nr, ne) those only some rows see; the row
-// statistics then cover [0, nr) only and are taken here, from the proxies themselves: the
-// proxies go to LDS (prox, nr floats), their mean and population deviation give
-// tau_i = mu_i + beta sigma_i, and the selection bits follow.  (Prefix moments of the pooled
-// keys would need a d x d matrix per query block.)
+// nr = NKr and ne = NK (the forced tail).  With a causal mask [0, nr) are the key blocks every row
+// of the query block sees and [nr, ne) those only some rows see.  With `direct` (causal masks:
+// prefix moments of the pooled keys would need a d x d matrix per query block; and callers without
+// a thresholds launch) the row statistics are taken here, from the proxies themselves: the proxies
+// go to LDS (prox, nr floats), their mean and population deviation over [0, nr) give
+// tau_i = mu_i + beta sigma_i, and the selection bits follow.
 // ---------------------------------------------------------------------------
 
 // Sum over the workgroup; every thread gets the total.  scratch: NT/64 floats.
@@ -678,10 +696,11 @@ __global__ __launch_bounds__(256) void order_kernel(const float* __restrict__ qb
         if (r < nmine) ord[rank[r]] = (uint16_t)(t + NT * r);
 }
 
-template <int D, int NT, int MODE, bool CAUSAL = false>
-__device__ int route_and_list(const float* __restrict__ qbar_i, const float* __restrict__ kbar_h, float tau_i,
-                              float beta, float scale, int NKr, int nr, int ne, int MW, float* prox, uint32_t* selw,
-                              uint16_t* list, int ucap, int* scan_scratch, int* wpre, int* nuns, int* nsel) {
+template <int D, int NT, int MODE>
+__device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, const float* __restrict__ kbar_h, bool direct,
+                              float tau_i, float beta, float scale, int nr, int ne, int MW, float* prox,
+                              uint32_t* selw, uint16_t* list, int ucap, int* scan_scratch, int* wpre, int* nuns,
+                              int* nsel) {
     const int NC = (nr + kChunk - 1) / kChunk;   // chunks of routable blocks
     constexpr int CPR = D / 4;              // 16-byte chunks per f32 pooled-key row
     constexpr int TPK = NT / kChunk;        // threads per pooled key (1, 2 or 4)
@@ -699,7 +718,7 @@ __device__ int route_and_list(const float* __restrict__ qbar_i, const float* __r
 #pragma unroll
     for (int i = 0; i < CPT; ++i) qv[i] = *reinterpret_cast<const f32x4*>(qbar_i + 4 * (seg + TPK * i));
     auto load = [&](int c, f32x4 (&kv)[CPT]) SOL_INLINE {
-        const float* rp = kbar_h + (size_t)min(c * kChunk + jl, nr - 1) * D;
+        const float* rp = kbar_h + (size_t)min(c * kChunk + jl, max(nr, 1) - 1) * D;
 #pragma unroll
         for (int i = 0; i < CPT; ++i) kv[i] = *reinterpret_cast<const f32x4*>(rp + 4 * (seg + TPK * i));
     };
@@ -720,7 +739,7 @@ __device__ int route_and_list(const float* __restrict__ qbar_i, const float* __r
         if constexpr (TPK >= 4)
             dot += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dot), 0x4E, 0xF, 0xF, false));
         const int j = c * kChunk + jl;
-        if constexpr (CAUSAL) {
+        if (direct) {
             if (seg == 0 && j < nr) prox[j] = scale * dot;
             return;
         }
@@ -780,8 +799,8 @@ __device__ int route_and_list(const float* __restrict__ qbar_i, const float* __r
     for (int b = 0; b < NB; ++b)
         if (c + NB + b < NC) decide(c + NB + b, kb[b]);
     __syncthreads();
-    if constexpr (CAUSAL) {
-        // row statistics over the routable prefix, then the selection bits of every word
+    if (direct) {
+        // row statistics over the routable blocks, then the selection bits of every word
         float* fscratch = reinterpret_cast<float*>(scan_scratch);
         float th = -kNegInf;
         if (nr > 0) {
@@ -798,13 +817,14 @@ __device__ int route_and_list(const float* __restrict__ qbar_i, const float* __r
             else if (beta == -kNegInf) th = -kNegInf;
             else th = mu + beta * sigma;
         }
-        for (int w = tid; w < MW; w += NT) {
-            uint32_t bits = 0u;
-            for (int b = 0; b < 32; ++b) {
-                const int j = 32 * w + b;
-                if (j < nr && prox[j] > th) bits |= 1u << b;
+        // a wave takes 64 blocks at a time: neighbouring lanes read neighbouring proxies
+        for (int j0 = 64 * wave; j0 < 32 * MW; j0 += NT) {
+            const int j = j0 + lane;
+            const uint64_t bal = __ballot(j < nr && prox[j] > th);
+            if (lane == 0) {
+                selw[j0 >> 5] = (uint32_t)bal;
+                if ((j0 >> 5) + 1 < MW) selw[(j0 >> 5) + 1] = (uint32_t)(bal >> 32);
             }
-            selw[w] = bits;
         }
         __syncthreads();
     }
@@ -1018,10 +1038,9 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
         nsel = nr;
     } else {
         const float tau_i = CAUSAL ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
-        ntiles = route_and_list<D, NT, MODE, CAUSAL>(a.qbar + ((size_t)bh * a.NQ + qi) * D,
-                                                     a.kbar + (size_t)bh * a.NK * D, tau_i, a.beta, a.scale, a.NKr,
-                                                     nr, ne, a.MW, prox, selw, list, a.NC * kChunk, scan_scratch,
-                                                     wpre, &nuns, &nsel);
+        ntiles = route_and_list<D, NT, MODE>(a.qbar + ((size_t)bh * a.NQ + qi) * D, a.kbar + (size_t)bh * a.NK * D,
+                                             CAUSAL, tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
+                                             a.NC * kChunk, scan_scratch, wpre, &nuns, &nsel);
         if (a.mask_out)
             for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
     }
@@ -1790,10 +1809,33 @@ __global__ void queue_reset_kernel(uint32_t* q) {
 }
 
 // ---------------------------------------------------------------------------
-// Routed attention with f32 inputs (correctness-first path, VALU only).  One thread per
-// query row; K/V (or pooled Kbar/Vbar for correction tiles) staged in LDS one tile at a
-// time; per-key streaming softmax in natural-exp units.
+// Routed attention with f32 inputs, on the f32 matrix instructions (v_mfma_f32_32x32x2_f32: f32
+// products and f32 sums, so nothing is rounded below 32 bits).
+//
+// What bounds it: the matrix pipe.  A wave takes 32 query rows; per 64-key tile at d = 128 it issues
+// 128 MFMAs of 64 cycles for QK^T and 128 for PV against about 2,000 cycles of softmax VALU work, and
+// one 16-byte operand read feeds four MFMAs (256 cycles).
+//   S^T = K Q^T  keys on MFMA rows, queries on lanes.  The instruction's two k values are lane halves:
+//                half hh holds d = 8u + 4hh + e in step 4u + e, so a lane's operands of four steps
+//                are 16 consecutive bytes of its key row.
+//   O^T += V^T P^T  accumulator register r of S^T holds key 8(r/4) + 4hh + r%4 of its lane's query,
+//                which is exactly the B operand of the step that takes the key pair (hh = 0, 1); the
+//                A operand comes from V rows as they are, lane l holding d = VE*l + e (VE = D/32), so
+//                accumulator e holds the d = VE*i + e and one read of two whole rows feeds VE MFMAs,
+//                without a transpose.
+// Keys and values of a tile are copied to LDS, one stage each (64 KB at d = 128: two workgroups a CU): the
+// keys of the next tile land while this one's softmax and PV run, its values during its QK^T, two
+// barriers per tile.  Reading V straight from the caches instead took 26,000 cycles per tile with one
+// wave per SIMD (the loads' latency), against 16,400 of MFMAs.
+// Query blocks of 64 rows have four waves too: two row slices times two key halves of every tile, the
+// halves' softmax states merged at the end through LDS.
+// A block's tiles (correction tiles, then exact ones) may be dealt in turn to several workgroups, each of
+// which then writes its unnormalised O and (m, l) for finish_kernel to merge: see f32_units.
+// Measured (whole forward): 8 heads of 4,255 tokens, d = 128, sparse, 22 % kept: 5,560 -> 273 us against one thread
+// per query row on the VALU; 2 heads of 2,048, d = 64: 790 -> 31 us; dense, 32 heads of 4,096, d = 128: 135 TFLOP/s
+// (a large f32 matrix product reaches 154 on the same card).
 // ---------------------------------------------------------------------------
+
 struct AttnArgsF32 {
     const float* q;
     const float* k;
@@ -1801,120 +1843,391 @@ struct AttnArgsF32 {
     const float* qbar;
     const float* kbar;
     const float* vbar;
-    const float* tau;
+    const float* tau;         // [BH][NQ], or null: each block takes its statistics from its own proxies
     float* out;
-    uint32_t* blkcount;
+    float* part;              // [slot][BQ][D] unnormalised O of the shares past a block's first
+    float* part_ml;           // [workgroup][BQ][2] running max (log2 units) and row sum
+    uint32_t* counts;
     uint32_t* mask_out;
     int BH, N, NQ, NK, NKr, NC, MW;
-    float scale;
+    F32Units units;
+    uint32_t dense_count;     // selected pairs of a head in dense mode
+    float scale, c_log2;
     int causal_g;
+    int prox_n;               // proxies a row keeps in LDS: NKr with statistics on chip, else 0
     float beta;
 };
 
+constexpr int kF32ProxMax = 4096;
+
+// LDS of the f32 kernel: a stage of 64 key rows and one of 64 value rows, scan scratch, selection words, lists,
+// word prefixes, a row's proxies (statistics on chip).
+struct LdsF32 {
+    size_t scan, selw, list, wpre, prox, bytes;
+    __host__ __device__ LdsF32(int d, int MW, int NC, int NK, int prox_n) {
+        const size_t mw4 = 4 * (size_t)((MW + 3) & ~3);
+        scan = 2 * (size_t)kBlockK * d * 4;
+        selw = scan + 64;
+        list = selw + mw4;
+        wpre = (list + 2 * ((size_t)NC * kChunk + NK) + 15) & ~(size_t)15;
+        prox = wpre + mw4;
+        bytes = prox + 4 * (size_t)prox_n;
+    }
+};
+
+// Workgroup u of the grid -> block b of the launch's block order (past the last one: nothing to do) and its share
+// sp of the block's ns shares.  Consecutive workgroups go round-robin to the 8 XCDs, each with its own L2, so
+// all shares of a block are dealt to one XCD; with the heads innermost in the block order and 8 of them,
+// every XCD then works on one head.
+__device__ inline void f32_unit(const F32Units& t, int u, int& b, int& sp, int& ns) {
+    const int first = t.nb1 * t.ns1, x = u & 7;   // nb1 is a multiple of 8, or all blocks
+    ns = u < first ? t.ns1 : t.ns2;
+    const int y = (u < first ? u : u - first) >> 3;
+    b = (u < first ? 0 : t.nb1) + (y / ns) * 8 + x;
+    sp = y % ns;
+}
+// Partial-output slot of share 1 of block b (the following shares follow; share 0 keeps its partial output in
+// the output itself), and (max, row sum) slot of share 0.
+__device__ inline int f32_slot(const F32Units& t, int b) {
+    return min(b, t.nb1) * (t.ns1 - 1) + max(b - t.nb1, 0) * (t.ns2 - 1);
+}
+__device__ inline int f32_ml_slot(const F32Units& t, int b) {
+    return min(b, t.nb1) * t.ns1 + max(b - t.nb1, 0) * t.ns2;
+}
+
 template <int D, int BQ, int MODE, bool CAUSAL>
-__global__ __launch_bounds__(BQ) void routed_attn_f32_kernel(AttnArgsF32 a) {
-    constexpr int NT = BQ;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void routed_attn_f32_kernel(AttnArgsF32 a) {
+    constexpr int NT = 256;
+    constexpr int RS = BQ / 32;       // row slices
+    constexpr int KG = 4 / RS;        // key halves of a tile, a wave each (64-row blocks), or one wave for all keys
+    constexpr int NM = 2 / KG;        // 32-key score tiles of a wave
+    constexpr int NU = D / 8;         // 16-byte operand reads per K row and lane
+    constexpr int VE = D / 32;        // d values per lane in a V row, output accumulators
+    constexpr int CPR = D / 4;        // 16-byte chunks per row
+    constexpr int RB = 4 * D;         // bytes per row
+    constexpr int STAGE = kBlockK * RB;
+    constexpr int CPW = STAGE / 1024 / 4;   // 1 KB copies per wave and stage
+    typedef float vecv __attribute__((ext_vector_type(VE)));
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    float* ks = reinterpret_cast<float*>(smem);            // [64][D]
-    float* vs = ks + kBlockK * D;                          // [64][D]
-    float* qt = vs + kBlockK * D;                          // [D][BQ]
-    char* rest = reinterpret_cast<char*>(qt + D * BQ);
-    int* scan_scratch = reinterpret_cast<int*>(rest);
-    uint32_t* selw = reinterpret_cast<uint32_t*>(rest + 64);
-    uint16_t* list = reinterpret_cast<uint16_t*>(rest + 64 + 4 * ((a.MW + 3) & ~3));
-    int* wpre = reinterpret_cast<int*>(rest + ((64 + 4 * ((a.MW + 3) & ~3) + 2 * (a.NC * kChunk + a.NK) + 15) & ~15));
-    float* prox = reinterpret_cast<float*>(wpre + ((a.MW + 3) & ~3));   // after the word prefixes
-    const uint16_t* ulist = list;            // correction slots (unselected routable blocks, padded)
+    const LdsF32 L(D, a.MW, a.NC, a.NK, a.prox_n);
+    int* scan_scratch = reinterpret_cast<int*>(smem + L.scan);
+    uint32_t* selw = reinterpret_cast<uint32_t*>(smem + L.selw);
+    uint16_t* list = reinterpret_cast<uint16_t*>(smem + L.list);
+    int* wpre = reinterpret_cast<int*>(smem + L.wpre);
+    float* prox = reinterpret_cast<float*>(smem + L.prox);
+    const uint16_t* ulist = list;                   // correction slots (unselected routable blocks, padded)
     const uint16_t* elist = list + a.NC * kChunk;   // exact tiles
 
-    const int bh = blockIdx.y, qi = blockIdx.x, tid = threadIdx.x;
-    int nr = a.NKr, ne = a.NK;               // routable blocks [0, nr), forced blocks [nr, ne)
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int blk, sp, ns;
+    f32_unit(a.units, blockIdx.x, blk, sp, ns);
+    sp = __builtin_amdgcn_readfirstlane(sp);   // divisions run on the VALU: back to scalar registers
+    ns = __builtin_amdgcn_readfirstlane(ns);
+    blk = __builtin_amdgcn_readfirstlane(blk);
+    if (blk >= a.BH * a.NQ) return;
+    const int bh = __builtin_amdgcn_readfirstlane(blk % a.BH), qx = __builtin_amdgcn_readfirstlane(blk / a.BH);
+    const int qi = CAUSAL ? a.NQ - 1 - qx : qx;     // causal masks: the longest blocks first
+    int nr = a.NKr, ne = a.NK;                      // routable blocks [0, nr), forced blocks [nr, ne)
     if constexpr (CAUSAL) causal_ranges<BQ>(qi, a.causal_g, a.N, a.NK, nr, ne);
     int ntiles, nsel, nuns = 0;
     if (MODE == kDense) {
         ntiles = ne;
-        nsel = nr;
+        if (tid == 0 && qx == 0 && sp == 0) a.counts[bh] = a.dense_count;
     } else {
-        const float tau_i = CAUSAL ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
-        ntiles = route_and_list<D, NT, MODE, CAUSAL>(a.qbar + ((size_t)bh * a.NQ + qi) * D,
-                                                     a.kbar + (size_t)bh * a.NK * D, tau_i, a.beta, a.scale, a.NKr,
-                                                     nr, ne, a.MW, prox, selw, list, a.NC * kChunk, scan_scratch,
-                                                     wpre, &nuns, &nsel);
-        if (a.mask_out)
-            for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
+        __builtin_amdgcn_s_setprio(3);   // a chain of latencies: ahead of the other workgroup's tiles
+        const bool direct = CAUSAL || a.tau == nullptr;
+        const float tau_i = direct ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
+        ntiles = route_and_list<D, NT, MODE>(a.qbar + ((size_t)bh * a.NQ + qi) * D, a.kbar + (size_t)bh * a.NK * D,
+                                             direct, tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
+                                             a.NC * kChunk, scan_scratch, wpre, &nuns, &nsel);
+        __builtin_amdgcn_s_setprio(0);
+        ntiles = __builtin_amdgcn_readfirstlane(ntiles);   // from LDS, the same in every lane: scalar control flow
+        nuns = __builtin_amdgcn_readfirstlane(nuns);
+        if (sp == 0) {
+            if (a.mask_out)
+                for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
+            if (tid == 0) atomicAdd(a.counts + bh, (uint32_t)nsel);
+        }
     }
-    if (tid == 0) a.blkcount[(size_t)bh * a.NQ + qi] = (uint32_t)nsel;
-
-    const int row = qi * BQ + tid;
-    const int qlim = CAUSAL ? causal_lim(row, a.causal_g, a.N) : a.N;   // this row sees keys < qlim
-    for (int e = tid; e < BQ * D; e += NT) {
-        const int rr = e / D, c = e % D, gr = qi * BQ + rr;
-        qt[c * BQ + rr] = gr < a.N ? a.q[((size_t)bh * a.N + gr) * D + c] : 0.f;
-    }
-    float o[D];
-#pragma unroll
-    for (int c = 0; c < D; ++c) o[c] = 0.f;
-    float m = kNegInf, l = 0.f;
-
-    // correction tiles first (64 unselected routable blocks each), then the exact tiles
     const int napx = MODE == kSparse ? (nuns + kChunk - 1) / kChunk : 0;
-    for (int n = 0; n < napx + ntiles; ++n) {
-        const bool apx = n < napx;
-        const int c = apx ? n : (MODE == kDense ? n : (int)elist[n - napx]);
-        __syncthreads();
-        for (int e = tid; e < kBlockK * D; e += NT) {
-            const int rr = e / D, cc = e % D;
-            float kv = 0.f, vv = 0.f;
-            if (apx) {
-                const int u = c * kChunk + rr;
-                if (u < nuns) {
-                    const int j = ulist[u];
-                    kv = a.kbar[((size_t)bh * a.NK + j) * D + cc];
-                    vv = a.vbar[((size_t)bh * a.NK + j) * D + cc];
-                }
-            } else {
-                const int gr = c * kBlockK + rr;
-                if (gr < a.N) {
-                    kv = a.k[((size_t)bh * a.N + gr) * D + cc];
-                    vv = a.v[((size_t)bh * a.N + gr) * D + cc];
-                }
-            }
-            ks[e] = kv;
-            vs[e] = vv;
-        }
-        __syncthreads();
-        for (int u = 0; u < kBlockK; ++u) {
-            float bias = 0.f;
-            if (apx) {
-                if (c * kChunk + u >= nuns) continue;
-                const int j = ulist[c * kChunk + u];
-                bias = logf((float)min(kBlockK, a.N - j * kBlockK));
-            } else if (c * kBlockK + u >= (CAUSAL && c >= nr ? qlim : a.N)) {
-                continue;
-            }
-            float dot = 0.f;
-#pragma unroll 16
-            for (int cc = 0; cc < D; ++cc) dot = fmaf(qt[cc * BQ + tid], ks[u * D + cc], dot);
-            const float s = dot * a.scale + bias;
-            if (s > m) {
-                const float alpha = m == kNegInf ? 0.f : expf(m - s);
-                l *= alpha;
+    const int T = napx + ntiles;
+
+    const int r32 = lane & 31, hh = lane >> 5;
+    const int rw = wave % RS, kg = wave / RS;       // row slice, key half
+    const int row = qi * BQ + rw * 32 + r32;
+    const int qlim = CAUSAL ? causal_lim(row, a.causal_g, a.N) : a.N;   // this row sees keys < qlim
+    f32x4 qf[NU];
+    {
+        const float* qp = a.q + ((size_t)bh * a.N + min(row, a.N - 1)) * D + 4 * hh;
 #pragma unroll
-                for (int cc = 0; cc < D; ++cc) o[cc] *= alpha;
-                m = s;
+        for (int u = 0; u < NU; ++u) qf[u] = *reinterpret_cast<const f32x4*>(qp + 8 * u);
+    }
+    f32x16 o[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) o[e] = f32x16{};
+    float m = kNegInf, l = 0.f;
+    const float cl = a.c_log2;
+
+    // LDS byte offset of chunk 2u + hh of key row r32 of this wave's keys, u < 8 (u + 8: 256 bytes on).  A row's
+    // chunks are XORed with the row, so that 16 rows reading one chunk column hit 16 bank groups.
+    uint32_t kadr[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+        kadr[u] = 16u * (uint32_t)((32 * NM * kg + r32) * CPR + ((2 * u + hh) ^ (r32 & 15)));
+
+    // Tile n of the block: kFullTile key block c, all 64 rows valid and seen by every query row; kEdgeTile key
+    // block c with a ragged end (nv rows) or a causal edge; kApxTile the pooled keys and value means of the
+    // list's slots [64 c, 64 c + nv).  Rows past nv are copied as the last valid one; their scores become
+    // -inf and their values 0.
+    enum { kFullTile, kEdgeTile, kApxTile };
+    auto tile_code = [&](int n, int& c, int& nv) SOL_INLINE -> int {
+        if (MODE == kSparse && n < napx) {
+            c = n;
+            nv = min(kChunk, nuns - n * kChunk);
+            return kApxTile;
+        }
+        c = __builtin_amdgcn_readfirstlane(MODE == kDense ? n : (int)elist[n - napx]);
+        nv = min(kBlockK, a.N - c * kBlockK);
+        return nv == kBlockK && !(CAUSAL && c >= nr) ? kFullTile : kEdgeTile;
+    };
+    // Copies tile n's rows of src (exact) or pooled (correction) to the stage at byte offset dst.
+    auto issue = [&](int n, const float* src, const float* pooled, bool swizzle, int dst) SOL_INLINE {
+        int c, nv;
+        const bool apx = tile_code(n, c, nv) == kApxTile;
+        const float* base = MODE == kSparse && apx ? pooled + (size_t)bh * a.NK * D
+                                                   : src + ((size_t)bh * a.N + (size_t)c * kBlockK) * D;
+        // The same address in every lane: scalar registers.  A scalar register written by the VALU may be read by
+        // a memory instruction five wait states later at the earliest; the compiler does not see the
+        // copies' inline assembly, so the wait is written here.
+        const uint64_t bits = reinterpret_cast<uint64_t>(base);
+        uint32_t b0 = __builtin_amdgcn_readfirstlane((int)(uint32_t)bits);
+        uint32_t b1 = __builtin_amdgcn_readfirstlane((int)(uint32_t)(bits >> 32));
+        asm volatile("s_nop 4" : "+s"(b0), "+s"(b1));
+        const void* sbase = reinterpret_cast<const void*>((uint64_t)b0 | (uint64_t)b1 << 32);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // per-lane offsets formed per tile, not kept through the loop
+        uint32_t off[CPW];
+#pragma unroll
+        for (int u = 0; u < CPW; ++u) {
+            const int p = (wave * CPW + u) * 64 + ln, r = p / CPR;
+            const int cc = swizzle ? (p % CPR) ^ (r & 15) : p % CPR;
+            int t = min(r, nv - 1);
+            if (MODE == kSparse && apx) t = ulist[c * kChunk + t];
+            off[u] = (uint32_t)(t * RB + cc * 16);
+        }
+#pragma unroll
+        for (int u = 0; u < CPW; ++u) lds_copy16(sbase, off[u], (lds_ptr_t)(smem + dst + (wave * CPW + u) * 1024));
+    };
+    auto landed = [&]() SOL_INLINE {   // this wave's copies have landed, then everyone's
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
+    // key within the tile of accumulator register i % 16 of score tile i / 16: kcon(i) + 4 hq
+    auto kcon = [](int i) SOL_INLINE -> int { return 32 * (i >> 4) + 8 * ((i & 15) >> 2) + (i & 3); };
+
+    auto tile = [&](auto kind_tag, const int c, const int nv, const int next) SOL_INLINE {
+        constexpr int KIND = decltype(kind_tag)::value;
+        constexpr bool APX = KIND == kApxTile;
+        const int k0 = 32 * NM * kg;   // this wave's first key of the tile
+        int hq = hh, lq = r32;
+        asm volatile("" : "+v"(hq), "+v"(lq));   // per-lane offsets formed per tile, not kept through the loop
+        auto ldk = [&](int u, int h) SOL_INLINE -> f32x4 {
+            return *reinterpret_cast<const f32x4*>(smem + kadr[u & 7] + (u >> 3) * 256 + h * 32 * RB);
+        };
+        // s[h]: score tile h, or with one score tile per wave the sums over even and odd u (two shorter chains)
+        f32x4 ka[2][NM];
+#pragma unroll
+        for (int h = 0; h < NM; ++h) ka[0][h] = ldk(0, h);
+        f32x16 s[2] = {f32x16{}, f32x16{}};
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            if (u + 1 < NU) {
+#pragma unroll
+                for (int h = 0; h < NM; ++h) ka[(u + 1) & 1][h] = ldk(u + 1, h);
             }
-            const float p = expf(s - m);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (NM == 2) {
+                    s[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[u & 1][0][e], qf[u][e], s[0], 0, 0, 0);
+                    s[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[u & 1][1][e], qf[u][e], s[1], 0, 0, 0);
+                } else {
+                    s[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[u & 1][0][e], qf[u][e], s[e & 1], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);   // the operand reads stay one step ahead, not all at the top
+        }
+        if constexpr (NM == 1) s[0] += s[1];
+        landed();   // the tile's values are in LDS, and its keys are read
+        const bool partial = CAUSAL && KIND == kEdgeTile && c >= nr;   // some rows see only a part of the tile
+        if (next < T && !partial) issue(next, a.k, a.kbar, true, 0);
+        // scores in log2 units; unselected blocks weigh n_j keys
+        float mt = kNegInf;
+        const int rel = CAUSAL && KIND == kEdgeTile ? min(nv, qlim - c * kBlockK) : nv;   // keys < rel count
+#pragma unroll
+        for (int i = 0; i < 16 * NM; ++i) {
+            float x = s[i >> 4][i & 15];
+            const int kt = k0 + kcon(i) + 4 * hq;
+            if constexpr (APX) {
+                const int j = ulist[c * kChunk + min(kt, nv - 1)];
+                x = fmaf(x, cl, log2f((float)min(kBlockK, a.N - j * kBlockK)));
+            }
+            if constexpr (KIND != kFullTile) x = kt < rel ? x : kNegInf;
+            s[i >> 4][i & 15] = x;
+            mt = fmaxf(mt, x);
+        }
+        if constexpr (!APX) mt *= cl;
+        {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
+            mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+        }
+        const bool need = mt > m + kRescaleSlack;
+        if (__ballot(need)) {
+            const float mnew = need ? mt : m;
+            const float alpha = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - mnew);
+#pragma unroll
+            for (int e = 0; e < VE; ++e) o[e] *= alpha;
+            l *= alpha;
+            m = mnew;
+        }
+        const float msub = m == kNegInf ? 0.f : m;
+#pragma unroll
+        for (int i = 0; i < 16 * NM; ++i) {
+            const float x = s[i >> 4][i & 15];
+            const float p = __builtin_amdgcn_exp2f(APX ? x - msub : fmaf(x, cl, -msub));
+            s[i >> 4][i & 15] = p;
             l += p;
-#pragma unroll
-            for (int cc = 0; cc < D; ++cc) o[cc] = fmaf(p, vs[u * D + cc], o[cc]);
         }
-    }
-    if (row < a.N) {
-        const float inv = l > 0.f ? 1.0f / l : 0.f;
-        float* op = a.out + ((size_t)bh * a.N + row) * D;
+        const char* vs = smem + STAGE + k0 * RB;
+        if (!partial) {
+            const char* vl = vs + (RB * 4 * hq + 4 * VE * lq);
+            auto ldv = [&](int i) SOL_INLINE -> vecv {
+                vecv x = *reinterpret_cast<const vecv*>(vl + kcon(i) * RB);
+                if constexpr (KIND != kFullTile)
+                    if (k0 + kcon(i) + 4 * hq >= nv) x = vecv{};
+                return x;
+            };
+            vecv va[2] = {ldv(0), vecv{}};
 #pragma unroll
-        for (int cc = 0; cc < D; ++cc) op[cc] = o[cc] * inv;
+            for (int i = 0; i < 16 * NM; ++i) {
+                if (i + 1 < 16 * NM) va[(i + 1) & 1] = ldv(i + 1);
+#pragma unroll
+                for (int e = 0; e < VE; ++e)
+                    o[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i & 1][e], s[i >> 4][i & 15], o[e], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if constexpr (CAUSAL) {
+            // Key by key on the VALU: a value that a row does not see must not enter its sum even as 0 times it
+            // (it may be infinite).  A few tiles of a block; the probabilities of 32 keys at a time pass
+            // through the key stage, which is free until the next tile's copy below.
+            float* pt = reinterpret_cast<float*>(smem) + wave * (32 * 32);
+            for (int h = 0; h < NM; ++h) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) pt[(kcon(i) + 4 * hq) * 32 + lq] = h ? s[1][i] : s[0][i];
+                __builtin_amdgcn_wave_barrier();   // the lane pair reads each other's writes
+                for (int kt = 0; kt < 32; ++kt) {
+                    const float p = pt[kt * 32 + lq];
+                    if (k0 + 32 * h + kt < rel) {
+                        const char* vr = vs + (32 * h + kt) * RB + 4 * VE * 4 * hq;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const vecv x = *reinterpret_cast<const vecv*>(vr + 4 * VE * (8 * (r >> 2) + (r & 3)));
+#pragma unroll
+                            for (int e = 0; e < VE; ++e) o[e][r] = fmaf(p, x[e], o[e][r]);
+                        }
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            __syncthreads();
+            if (next < T) issue(next, a.k, a.kbar, true, 0);
+        }
+    };
+
+    if (sp < T) issue(sp, a.k, a.kbar, true, 0);
+    for (int n = sp; n < T; n += ns) {
+        landed();   // the tile's keys are in LDS, and the previous tile's values are read
+        issue(n, a.v, a.vbar, false, STAGE);
+        int c, nv;
+        const int kind = tile_code(n, c, nv);
+        if (MODE == kSparse && kind == kApxTile) tile(std::integral_constant<int, kApxTile>{}, c, nv, n + ns);
+        else if (kind == kFullTile) tile(std::integral_constant<int, kFullTile>{}, c, kBlockK, n + ns);
+        else tile(std::integral_constant<int, kEdgeTile>{}, c, nv, n + ns);
     }
+
+    float lt = l + __shfl_xor(l, 32);
+    if constexpr (KG == 2) {
+        // the second key half hands its state to the first through LDS (the stages are free)
+        static_assert(2 * (VE * 16 + 2) * 64 * 4 <= 2 * STAGE, "exchange buffer exceeds the stages");
+        __syncthreads();
+        float* x = reinterpret_cast<float*>(smem) + rw * ((VE * 16 + 2) * 64) + lane;
+        if (kg == 1) {
+#pragma unroll
+            for (int e = 0; e < VE; ++e)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) x[(16 * e + r) * 64] = o[e][r];
+            x[16 * VE * 64] = m;
+            x[(16 * VE + 1) * 64] = lt;
+        }
+        __syncthreads();
+        if (kg == 1) return;
+        const float mp = x[16 * VE * 64], lp = x[(16 * VE + 1) * 64], mm = fmaxf(m, mp);
+        const float a0 = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - mm);
+        const float a1 = mp == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mp - mm);
+#pragma unroll
+        for (int e = 0; e < VE; ++e)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[e][r] = a0 * o[e][r] + a1 * x[(16 * e + r) * 64];
+        lt = a0 * lt + a1 * lp;
+        m = mm;
+    }
+    if (row >= a.N) return;
+    float inv = 1.f;
+    float* op = a.out + ((size_t)bh * a.N + row) * D;
+    if (ns > 1) {
+        const size_t r = rw * 32 + r32;
+        if (sp > 0) op = a.part + ((size_t)(f32_slot(a.units, blk) + sp - 1) * BQ + r) * D;
+        if (hh == 0)
+            *reinterpret_cast<float2*>(a.part_ml + 2 * ((size_t)(f32_ml_slot(a.units, blk) + sp) * BQ + r)) = make_float2(m, lt);
+    } else {
+        inv = lt > 0.f ? 1.0f / lt : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        vecv x;
+#pragma unroll
+        for (int e = 0; e < VE; ++e) x[e] = o[e][r] * inv;
+        *reinterpret_cast<vecv*>(op + VE * (8 * (r >> 2) + 4 * hh + (r & 3))) = x;
+    }
+}
+
+// Merges the partial states of the blocks that several workgroups shared: O = sum_s a_s O_s / sum_s a_s l_s with
+// a_s = 2^(m_s - max m).  grid (BQ * D / 1024, blocks from `first` on), one thread per four output values.
+template <int D, int BQ, bool CAUSAL>
+__global__ __launch_bounds__(256) void finish_kernel(const float* __restrict__ part, const float* __restrict__ ml,
+                                                     float* out, F32Units t, int first, int BH, int N,
+                                                     int NQ) {
+    const int blk = first + blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;   // i: 4-value group of the block
+    const int ns = blk < t.nb1 ? t.ns1 : t.ns2;
+    const int bh = blk % BH, qx = blk / BH, r = i / (D / 4);
+    const int row = (CAUSAL ? NQ - 1 - qx : qx) * BQ + r;
+    if (row >= N) return;
+    ml += 2 * ((size_t)f32_ml_slot(t, blk) * BQ + r);
+    part += (size_t)f32_slot(t, blk) * BQ * D + 4 * (size_t)i;
+    float* o = out + ((size_t)bh * N + row) * D + 4 * (i % (D / 4));
+    float mm = kNegInf;
+    for (int s = 0; s < ns; ++s) mm = fmaxf(mm, ml[2 * s * BQ]);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+    for (int s = 0; s < ns; ++s) {
+        const float ms = ml[2 * s * BQ];
+        const float w = ms == kNegInf ? 0.f : __builtin_amdgcn_exp2f(ms - mm);
+        l = fmaf(w, ml[2 * s * BQ + 1], l);
+        const f32x4 x = *reinterpret_cast<const f32x4*>(s == 0 ? o : part + (size_t)(s - 1) * BQ * D);
+        if (w > 0.f) acc += w * x;
+    }
+    *reinterpret_cast<f32x4*>(o) = acc * (l > 0.f ? 1.0f / l : 0.f);
 }
 
 __global__ __launch_bounds__(256) void count_reduce_kernel(const uint32_t* __restrict__ blk, uint32_t* __restrict__ counts,
@@ -1960,11 +2273,18 @@ hipError_t launch_attn_bf16(const Shape& s, const AttnArgs& a, hipStream_t st) {
 
 template <int D, int BQ, int MODE, bool CAUSAL>
 hipError_t launch_attn_f32(const Shape& s, const AttnArgsF32& a, hipStream_t st) {
-    const size_t lds = attn_lds_bytes(s);
+    const size_t lds = LdsF32(D, a.MW, a.NC, a.NK, a.prox_n).bytes;
     auto kern = routed_attn_f32_kernel<D, BQ, MODE, CAUSAL>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
-    kern<<<dim3(a.NQ, a.BH), dim3(BQ), lds, st>>>(a);
+    const F32Units& t = a.units;
+    const int blocks = a.BH * a.NQ;
+    kern<<<dim3(t.grid(blocks)), dim3(256), lds, st>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int first = t.ns1 > 1 ? 0 : t.nb1;   // blocks before it are whole
+    if (t.units(blocks) == blocks) return hipSuccess;
+    finish_kernel<D, BQ, CAUSAL><<<dim3(BQ * D / 1024, blocks - first), dim3(256), 0, st>>>(a.part, a.part_ml, a.out, t,
+                                                                                           first, a.BH, a.N, a.NQ);
     return hipGetLastError();
 }
 
@@ -2033,6 +2353,36 @@ size_t attn_lds_bytes(const Shape& s) {
     return (size_t)2 * kBlockK * s.d * 4 + (size_t)s.d * s.bq * 4 + rest;
 }
 
+// How many workgroups share a query block of the f32 kernel.  The chip holds 512 of them, two a CU; a block
+// costs what its tiles cost, whose number only the routing knows.  Measured (us, this rule against whole
+// blocks): 64 blocks of 64 rows, d = 64, sparse (2 heads, 2,048 tokens) 31 against 53; 24 dense blocks (2 heads,
+// 1,500 tokens, d = 128) 52 against 206; 272 sparse blocks (8 heads, 4,255 tokens, d = 128) 272 against 401,
+// 1,632 of them (48 heads) 1,286 against 1,392.
+//   fewer than 128 blocks   as many shares as give every CU one, up to 8; twice that under a causal mask,
+//                           where a block's tiles grow with its index
+//   fewer than 512          two shares for the first three quarters, six for the rest: the small shares fill
+//                           the CUs whose blocks were short
+//   more                    whole blocks, and four shares for the last 128, which even out the end
+// No more shares than leave four key blocks each, and partial outputs only within kSplitRoom.
+F32Units f32_units(const Shape& s, size_t base_bytes) {
+    const int blocks = s.BH * s.NQ, all = (blocks + 7) / 8 * 8;
+    const int most = std::max(1, std::min(8, s.NK / 4));
+    F32Units t;
+    if (blocks < 128) {
+        t.nb1 = all;
+        t.ns1 = std::min(most, std::max(1, 256 / blocks) * (s.causal ? 2 : 1));
+    } else if (blocks < 512) {
+        t.nb1 = blocks * 3 / 4 / 8 * 8;
+        t.ns1 = std::min(most, 2);
+        t.ns2 = std::min(most, 6);
+    } else {
+        t.nb1 = (blocks - 128) / 8 * 8;
+        t.ns2 = std::min(most, 4);
+    }
+    if (base_bytes + t.bytes(blocks, s.bq, s.d) > kSplitRoom) t = F32Units{all, 1, 1};
+    return t;
+}
+
 size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> char* {
@@ -2062,8 +2412,21 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
     } else if (s.mode == kSparse) {
         w.vbar = reinterpret_cast<float*>(take(BH * s.NK * d * 4));
     }
-    w.blkcount = reinterpret_cast<uint32_t*>(take(BH * s.NQ * 4));
+    if (s.dtype == kBF16) w.blkcount = reinterpret_cast<uint32_t*>(take(BH * s.NQ * 4));
     if (s.dtype == kBF16) w.queue = reinterpret_cast<uint32_t*>(take(8 * 32 * 4));
+    if (s.dtype == kF32) {
+        // The workspace query does not know about a mask: the room for partial outputs covers both cases.
+        Shape other = s;
+        other.causal = s.causal ? 0 : 1;
+        const int blocks = s.BH * s.NQ;
+        w.units = f32_units(s, off);
+        const size_t room = std::max(w.units.bytes(blocks, s.bq, s.d), f32_units(other, off).bytes(blocks, s.bq, s.d));
+        if (room > 0) {
+            char* p = take(room);
+            w.part = reinterpret_cast<float*>(p);
+            w.part_ml = reinterpret_cast<float*>(p + w.units.slots(blocks) * s.bq * d * 4);
+        }
+    }
     if (ws) *ws = w;
     return off;
 }
@@ -2148,6 +2511,17 @@ int heads_in_flight_log2(const Shape& s) {
     return hl;
 }
 
+// Selected (query block, key block) pairs of a head in dense mode: every routable one.
+uint32_t dense_count(const Shape& s) {
+    if (!s.causal) return (uint32_t)s.NQ * (uint32_t)s.NKr;
+    uint32_t tot = 0;
+    for (int i = 0; i < s.NQ; ++i) {
+        const long long lo = std::min<long long>(((long long)i * s.bq / s.causal + 1) * s.causal, s.N);
+        tot += lo >= s.N ? (uint32_t)s.NK : (uint32_t)(lo / s.bk);
+    }
+    return tot;
+}
+
 hipError_t launch_forward(const Shape& s, const void* q, const void* k, const void* v, void* out, float beta,
                           const Workspace& ws, uint32_t* counts, uint32_t* mask_out, hipStream_t st,
                           hipEvent_t ev_start, hipEvent_t ev_stop) {
@@ -2208,12 +2582,16 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         if (e != hipSuccess) return e;
         if (ev_stop && (e = hipEventRecord(ev_stop, st)) != hipSuccess) return e;
     } else {
+        // Each block takes its statistics from its own proxies (no moments, no thresholds launch): a wave's share
+        // of that is a few thousand cycles against 16,000 for one tile.  The diagonal estimator needs the
+        // moments; so do proxy rows past kF32ProxMax, which would not leave room for two workgroups a CU.
+        const bool moments = routing && !s.causal && (s.diag || s.NKr > kF32ProxMax);
         if (routing) {
-            if ((e = launch_pool_mean(q, ws.qbar, kF32, s.BH, s.N, d, s.bq, st)) != hipSuccess) return e;
-            if ((e = launch_pool_mean(k, ws.kbar, kF32, s.BH, s.N, d, s.bk, st)) != hipSuccess) return e;
-            if (s.mode == kSparse && (e = launch_pool_mean(v, ws.vbar, kF32, s.BH, s.N, d, s.bk, st)) != hipSuccess)
-                return e;
-            if (!s.causal) {
+            prep_f32_kernel<<<dim3(s.NQ + (s.mode == kSparse ? 2 : 1) * s.NK, s.BH), dim3(256), 0, st>>>(
+                static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v), ws.qbar,
+                ws.kbar, ws.vbar, counts, s.N, d, s.bq, s.NQ, s.NK);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            if (moments) {
                 if ((e = launch_moments(ws.kbar, ws.muk, ws.cov, ws.mom, s.BH, s.NK, s.NKr, d, st)) != hipSuccess)
                     return e;
                 if ((e = launch_tau(ws.qbar, ws.muk, ws.cov, ws.tau, nullptr, nullptr, s.BH, s.NQ, d, beta, s.diag,
@@ -2228,12 +2606,18 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.qbar = ws.qbar;
         a.kbar = ws.kbar;
         a.vbar = ws.vbar;
-        a.tau = ws.tau;
+        a.tau = moments ? ws.tau : nullptr;
+        a.prox_n = routing && !moments ? s.NKr : 0;
         a.out = static_cast<float*>(out);
-        a.blkcount = ws.blkcount;
+        a.part = ws.part;
+        a.part_ml = ws.part_ml;
+        a.counts = counts;
         a.mask_out = mask_out;
         a.BH = s.BH; a.N = s.N; a.NQ = s.NQ; a.NK = s.NK; a.NKr = s.NKr; a.NC = s.NC; a.MW = s.MW;
+        a.units = ws.units;
+        a.dense_count = routing ? 0u : dense_count(s);
         a.scale = scale;
+        a.c_log2 = scale * kLog2e;
         a.causal_g = s.causal;
         a.beta = beta;
         if (ev_start && (e = hipEventRecord(ev_start, st)) != hipSuccess) return e;
@@ -2241,6 +2625,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         else e = s.bq == 128 ? dispatch_f32<64, 128>(s, a, st) : dispatch_f32<64, 64>(s, a, st);
         if (e != hipSuccess) return e;
         if (ev_stop && (e = hipEventRecord(ev_stop, st)) != hipSuccess) return e;
+        return hipSuccess;
     }
     count_reduce_kernel<<<dim3(s.BH), dim3(256), 0, st>>>(ws.blkcount, counts, s.NQ);
     return hipGetLastError();

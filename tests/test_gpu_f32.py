@@ -1,0 +1,86 @@
+"""f32 inputs: the sharing of query blocks between workgroups, tile edges, masked values and long rows, against the
+fp64 oracle with the f32 tolerances of the other parity tests."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import sol_attn_oracle as ora
+from paper_2607_24027_amd import binding as sb
+from paper_2607_24027_amd import synth
+from tests.parity import assert_mask_matches, assert_output_close, small_workload, to_np
+
+pytestmark = pytest.mark.gpu
+
+# (H, N, d, block_q, granule, mode): every rule of the sharing (fewer than 128 query blocks, fewer than 512, more), both
+# block heights and head sizes, last blocks of 1 and 63 rows, none, and of a full block.
+CASES = [
+    (1, 63, 64, 64, 0, "dense"),
+    (2, 1024, 128, 64, 0, "sparse"),
+    (3, 1025, 128, 128, 0, "sparse"),
+    (2, 1087, 64, 128, 0, "sparse_no_correction"),
+    (7, 2497, 64, 128, 0, "sparse"),            # 140 query blocks, not a multiple of 8
+    (17, 1984, 64, 64, 0, "sparse"),            # 527 query blocks
+    (17, 1985, 64, 64, 0, "dense"),
+    (2, 1025, 128, 128, 1, "dense"),
+    (2, 1025, 128, 64, 100, "sparse"),
+    (5, 1903, 64, 64, 1, "sparse"),             # 150 query blocks
+    (18, 1921, 64, 64, 130, "sparse_no_correction"),   # 558 query blocks
+]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    sb.lib()
+    return torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("H,N,d,bq,g,mode", CASES)
+def test_f32_shared_blocks_parity(dev, H, N, d, bq, g, mode):
+    w = small_workload("f32", (N,), d, bq, dtype="f32", H=H, seed=5 + N)
+    q, k, v = synth.make_qkv(w)
+    print(f"[f32] H={H} N={N} d={d} bq={bq} G={g} {mode}", flush=True)
+    mask = torch.zeros((1, H, w.NQ, sb.mask_words(w.NK)), dtype=torch.int32, device=dev)
+    counts = torch.full((1, H), -1, dtype=torch.int32, device=dev)
+    out = torch.full(q.shape, math.nan, device=dev)
+    sb.forward(q.to(dev), k.to(dev), v.to(dev), bq, 64, 0.5, mode, out=out, counts=counts, mask_out=mask, causal_granule=g)
+    torch.cuda.synchronize()
+    qn, kn, vn = to_np(q), to_np(k), to_np(v)
+    ref = ora.forward(qn, kn, vn, bq, 64, 0.5, mode, causal_granule=g)
+    if mode != "dense":
+        gmask = sb.unpack_mask(mask.cpu().numpy().view(np.uint32), w.NK)
+        if assert_mask_matches(gmask, ref["mask"], ref["s_hat"], ref["tau"]):
+            ref = ora.forward(qn, kn, vn, bq, 64, 0.5, mode, causal_granule=g, mask=gmask)
+        assert np.array_equal(counts.cpu().numpy(), gmask.sum(axis=(2, 3)))
+    assert_output_close(to_np(out), ref["out"], "f32", mode)
+
+
+@pytest.mark.parametrize("d,bq", [(64, 64), (128, 128)])
+def test_f32_causal_masked_values_do_not_enter(dev, d, bq):
+    # the last token's value is infinite: only the last row may see it
+    w = small_workload("f32inf", (700,), d, bq, dtype="f32", H=2, seed=3)
+    q, k, v = synth.make_qkv(w)
+    ref = sb.forward(q.to(dev), k.to(dev), v.to(dev), bq, 64, 0.0, "dense", causal_granule=1)
+    v[:, :, -1] = math.inf
+    out = sb.forward(q.to(dev), k.to(dev), v.to(dev), bq, 64, 0.0, "dense", causal_granule=1)
+    assert torch.equal(out[:, :, :-1], ref[:, :, :-1])
+    assert bool((out[:, :, -1] == math.inf).all())
+
+
+def test_f32_long_rows_take_the_moment_thresholds(dev):
+    # 4,099 key blocks: past the rows whose statistics are taken on chip
+    w = small_workload("f32long", (2, 262, 501), 64, 128, dtype="f32", H=1, seed=9)
+    assert w.NK > 4096
+    q, k, v = synth.make_qkv(w)
+    mask = torch.zeros((1, 1, w.NQ, sb.mask_words(w.NK)), dtype=torch.int32, device=dev)
+    out = sb.forward(q.to(dev), k.to(dev), v.to(dev), 128, 64, 1.5, "sparse", mask_out=mask)
+    gmask = sb.unpack_mask(mask.cpu().numpy().view(np.uint32), w.NK)
+    qn, kn, vn = to_np(q), to_np(k), to_np(v)
+    rows = [0, w.NQ // 2, w.NQ - 1]
+    ref = ora.forward(qn, kn, vn, 128, 64, 1.5, "sparse", query_blocks=rows, mask=gmask)
+    s_hat = (ora.pool_means(qn, 128)[0] @ ora.pool_means(kn, 64)[0].transpose(0, 1, 3, 2)) / 8.0
+    tau = s_hat.mean(-1) + 1.5 * s_hat.std(-1)
+    assert_mask_matches(gmask, s_hat > tau[..., None], s_hat, tau)
+    assert_output_close(to_np(out), ref["out"], "f32", "long")
