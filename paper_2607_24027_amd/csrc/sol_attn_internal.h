@@ -62,7 +62,6 @@ struct Workspace {
     float* sigma = nullptr;      // [BH][NQ] sigma_i of the thresholds (query-block order)
     uint16_t* order = nullptr;   // [BH][NQ] query-block order of the sparse kernels
     double* mom = nullptr;       // partial moments, moments_scratch_bytes()
-    uint32_t* blkcount = nullptr;// [BH][NQ]
     uint32_t* queue = nullptr;   // [8][32] per-XCD claim counters of the bf16 attention kernel (one per 128 B)
     float* part = nullptr;       // [slot][bq][d] partial outputs of shared query blocks (f32 path)
     float* part_ml = nullptr;    // [workgroup][bq][2] running maxima and row sums

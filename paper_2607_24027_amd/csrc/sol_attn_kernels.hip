@@ -1,20 +1,20 @@
 // gfx950 kernels of the Sol-Attn forward pass.
 //
 // Pipeline of one forward (bf16 inputs):
-//   1. pool_mean      Qbar_i = token mean of query block i           (Eq. block_proxy)
-//   2. prep_kv        Kbar_j (f32 + f16 copy), Vbar_j (f16, correction layout) and the
-//                     f16 transposed V used by the exact tiles
-//   3. moments        mean and centred covariance of the routable pooled keys, f64 sums
-//   4. tau            tau_i = mu_i + beta*sigma_i from the moments   (Eqs. threshold_routing,
+//   1. prep           Qbar_i = token mean of query block i (Eq. block_proxy); Kbar_j (f32 + f16 copy), Vbar_j
+//                     (f16, correction layout) and the f16 transposed V used by the exact tiles;
+//                     claim counters and counts set
+//   2. moments        mean and centred covariance of the routable pooled keys, f64 sums
+//   3. tau            tau_i = mu_i + beta*sigma_i from the moments   (Eqs. threshold_routing,
 //                                                                       threshold_stats_exact)
-//   4b. order         sparse modes: order of each head's query blocks in the attention
-//                     kernel's work queues (scheduling: blocks with similar selections share an L2)
-//   5. routed_attn    persistent workgroups claim (b, h, query block) items from per-XCD
+//   3b. order         order of each head's query blocks in the attention kernel's work queues
+//                     (scheduling: blocks with similar selections share an L2)
+//                     2 to 3b only for long heads and the diagonal estimator (direct_stats)
+//   4. routed_attn    persistent workgroups claim (b, h, query block) items from per-XCD
 //                     queues; per block: route every key block on chip from f32 proxies, then
 //                     one online-softmax pass over correction tiles (pooled keys, Section 3.2
 //                     "Proxy-Score Reuse") and exact tiles (selected key blocks), with bf16
-//                     MFMA for QK^T and f16 MFMA for PV
-//   6. count_reduce   per-head number of selected routable pairs
+//                     MFMA for QK^T and f16 MFMA for PV; the head's count of selected pairs
 //
 // Tile math (wave64, v_mfma_f32_32x32x16_{bf16,f16}): each wave owns 32 query rows and
 // computes the transposed score tile S^T = K Q^T (keys on MFMA rows, queries on lanes), so a
@@ -99,9 +99,8 @@ struct Elem<float> {
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ void pool_mean_block(const T* __restrict__ x, float* __restrict__ mean, int N, int D,
-                                                int blk, int nb, int j, int bh) {
-    constexpr int EPC = Elem<T>::kPerChunk;
-    __shared__ float red[256 * EPC];
+                                                int blk, int nb, int j, int bh, float* red) {
+    constexpr int EPC = Elem<T>::kPerChunk;   // red: 256 * EPC floats of LDS
     const int t = threadIdx.x;
     const int cpr = D / EPC;
     const int groups = 256 / cpr;
@@ -133,7 +132,8 @@ __device__ __forceinline__ void pool_mean_block(const T* __restrict__ x, float* 
 template <typename T>
 __global__ __launch_bounds__(256) void pool_mean_kernel(const T* __restrict__ x, float* __restrict__ mean,
                                                         int N, int D, int blk, int nb) {
-    pool_mean_block<T>(x, mean, N, D, blk, nb, blockIdx.x, blockIdx.y);
+    __shared__ float red[256 * Elem<T>::kPerChunk];
+    pool_mean_block<T>(x, mean, N, D, blk, nb, blockIdx.x, blockIdx.y, red);
 }
 
 // The f32 forward's pooling in one launch: grid (NQ + NK [+ NK], BH), the query blocks, then the key
@@ -143,6 +143,7 @@ __global__ __launch_bounds__(256) void prep_f32_kernel(const float* __restrict__
                                                        float* __restrict__ kbar, float* __restrict__ vbar,
                                                        uint32_t* __restrict__ counts, int N, int D, int bq, int NQ,
                                                        int NK) {
+    __shared__ float red[256 * Elem<float>::kPerChunk];
     const int bh = blockIdx.y;
     int j = blockIdx.x;
     if (j == 0 && threadIdx.x == 0) counts[bh] = 0u;
@@ -151,11 +152,15 @@ __global__ __launch_bounds__(256) void prep_f32_kernel(const float* __restrict__
     const bool isv = !isq && j >= NK;
     if (isv) j -= NK;
     pool_mean_block<float>(isq ? q : isv ? v : k, isq ? qbar : isv ? vbar : kbar, N, D, isq ? bq : kBlockK,
-                           isq ? NQ : NK, j, bh);
+                           isq ? NQ : NK, j, bh, red);
 }
 
 // ---------------------------------------------------------------------------
-// K/V preparation for the bf16 forward.  grid (NJ, BH), 256 threads, one key block each.
+// Pre-pass of the bf16 forward, one launch.  grid (NJ [+ NQ], BH), 256 threads: one key block each, then (routing
+// modes) one query block each, whose means go to qbar; it also sets what the attention kernel
+// adds to: the claim counters and the heads' counts of selected pairs (0, or in dense mode the final
+// value).  As launches of their own the query means, the counter reset and the sum of per-block
+// counts cost about 4 us each in calls of a few hundred tokens.
 //   vt     [BH][NK][D][64] f16: V^T tile by tile (each key block's transposed values are
 //          one contiguous 16 KB run at d = 128), swap23 key order inside each 16-key
 //          segment; rows past N are zero.
@@ -167,10 +172,13 @@ __global__ __launch_bounds__(256) void prep_f32_kernel(const float* __restrict__
 // Blocks j >= NK exist only to zero the padding rows of the last correction tile.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(256) void prep_kv_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+__global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                       float* __restrict__ kbar, _Float16* __restrict__ kbarh,
                                                       _Float16* __restrict__ vbarh, _Float16* __restrict__ vt,
-                                                      int N, int NK, int NKr, int NC, int routing) {
+                                                      int N, int NK, int NKr, int NC, int routing,
+                                                      const uint16_t* __restrict__ q, float* __restrict__ qbar, int bq,
+                                                      int NQ, int NJ, uint32_t* __restrict__ queue,
+                                                      uint32_t* __restrict__ counts, uint32_t count0) {
     constexpr int CPR = D / 8;          // 16-byte chunks per row
     constexpr int GROUPS = 256 / CPR;   // row groups
     constexpr int VS = D + 2;           // f16 row stride of the staged V tile (odd word count)
@@ -178,6 +186,16 @@ __global__ __launch_bounds__(256) void prep_kv_kernel(const uint16_t* __restrict
     __shared__ float red[GROUPS * D];
     const int j = blockIdx.x, bh = blockIdx.y, t = threadIdx.x;
     const int cc = t % CPR, g = t / CPR;
+
+    if (j == 0) {
+        if (t == 0) counts[bh] = count0;
+        if (bh == 0 && t < 8) queue[32 * t] = 0u;
+    }
+    if (j >= NJ) {
+        static_assert(GROUPS * D == 256 * Elem<uint16_t>::kPerChunk, "pooling scratch");
+        pool_mean_block<uint16_t>(q, qbar, N, D, bq, NQ, j - NJ, bh, red);
+        return;
+    }
 
     if (j >= NK) {  // padding rows of the last correction tile
         for (int c = t; c < D; c += 256) {
@@ -874,11 +892,11 @@ struct AttnArgs {
     const float* kbar;
     const _Float16* kbarh;
     const _Float16* vbarh;
-    const float* tau;
+    const float* tau;             // [BH][NQ], or null: each block takes its statistics from its own proxies
     uint16_t* out;
-    uint32_t* blkcount;
+    uint32_t* counts;             // [BH] selected pairs, added to in the routing modes
     uint32_t* mask_out;
-    const uint16_t* order;        // [BH][NQ] query-block order (sparse modes), or null: identity
+    const uint16_t* order;        // [BH][NQ] query-block order, or null: identity
     uint32_t* queue;              // [8][32] per-XCD claim counters, zero at launch
     int resident;                 // workgroups per XCD in the persistent grid (grid / 8)
     int hlog;                     // log2 of the heads whose blocks are in the queues at once (no causal mask)
@@ -1037,14 +1055,15 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
         ntiles = ne;
         nsel = nr;
     } else {
-        const float tau_i = CAUSAL ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
+        const bool direct = CAUSAL || a.tau == nullptr;
+        const float tau_i = direct ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
         ntiles = route_and_list<D, NT, MODE>(a.qbar + ((size_t)bh * a.NQ + qi) * D, a.kbar + (size_t)bh * a.NK * D,
-                                             CAUSAL, tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
+                                             direct, tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
                                              a.NC * kChunk, scan_scratch, wpre, &nuns, &nsel);
         if (a.mask_out)
             for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
     }
-    if (tid == 0) a.blkcount[(size_t)bh * a.NQ + qi] = (uint32_t)nsel;
+    if (MODE != kDense && tid == 0) atomicAdd(a.counts + bh, (uint32_t)nsel);
     const int napx = MODE == kSparse ? (nuns + kChunk - 1) / kChunk : 0;   // correction tiles
     // slot of the ragged last key block among the correction slots (it can only be the last one)
     const int last_slot = (nuns > 0 && a.NKr == a.NK && ulist[max(nuns - 1, 0)] == a.NK - 1) ? nuns - 1 : -1;
@@ -1804,10 +1823,6 @@ void routed_attn_kernel(AttnArgs a) {
     }
 }
 
-__global__ void queue_reset_kernel(uint32_t* q) {
-    if (threadIdx.x < 8) q[32 * threadIdx.x] = 0u;
-}
-
 // ---------------------------------------------------------------------------
 // Routed attention with f32 inputs, on the f32 matrix instructions (v_mfma_f32_32x32x2_f32: f32
 // products and f32 sums, so nothing is rounded below 32 bits).
@@ -2230,19 +2245,6 @@ __global__ __launch_bounds__(256) void finish_kernel(const float* __restrict__ p
     *reinterpret_cast<f32x4*>(o) = acc * (l > 0.f ? 1.0f / l : 0.f);
 }
 
-__global__ __launch_bounds__(256) void count_reduce_kernel(const uint32_t* __restrict__ blk, uint32_t* __restrict__ counts,
-                                                           int NQ) {
-    __shared__ uint32_t red[4];
-    const int bh = blockIdx.x, t = threadIdx.x;
-    uint32_t s = 0;
-    for (int i = t; i < NQ; i += 256) s += blk[(size_t)bh * NQ + i];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if ((t & 63) == 0) red[t >> 6] = s;
-    __syncthreads();
-    if (t == 0) counts[bh] = red[0] + red[1] + red[2] + red[3];
-}
-
 template <typename K>
 hipError_t allow_lds(K kernel, size_t bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -2412,7 +2414,6 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
     } else if (s.mode == kSparse) {
         w.vbar = reinterpret_cast<float*>(take(BH * s.NK * d * 4));
     }
-    if (s.dtype == kBF16) w.blkcount = reinterpret_cast<uint32_t*>(take(BH * s.NQ * 4));
     if (s.dtype == kBF16) w.queue = reinterpret_cast<uint32_t*>(take(8 * 32 * 4));
     if (s.dtype == kF32) {
         // The workspace query does not know about a mask: the room for partial outputs covers both cases.
@@ -2522,6 +2523,19 @@ uint32_t dense_count(const Shape& s) {
     return tot;
 }
 
+// Whether the bf16 attention kernel takes each row's statistics from its own proxies, without the moments,
+// thresholds and query-block-order launches (the causal kernels always do; the diagonal estimator
+// needs the moments).  Those four launches cost 35 us in the shortest calls and 80-120 us at 480p and image
+// sizes; what they buy is the query-block order's L2 hits, which grow with a head's blocks.  Whole
+// forwards without them: 17 key blocks a head 60 -> 26 us, 85 x 170 (query x key blocks) 321 -> 293, 264 x 264
+// 3,174 -> 3,103, 256 x 512 1,893 -> 1,848; but 313 x 625 4,750 -> 4,793, 513 x 513 3,761 -> 3,863, 591 x 1182
+// 23,740 -> 24,200 us.
+constexpr long long kDirectMaxPairs = 150000;
+bool direct_stats(const Shape& s) {
+    return !s.causal && !s.diag && (long long)s.NQ * s.NKr <= kDirectMaxPairs &&
+           4 * (long long)s.NKr <= 4LL * kBlockK * s.d * 2;   // the proxies fit in the tile stages
+}
+
 hipError_t launch_forward(const Shape& s, const void* q, const void* k, const void* v, void* out, float beta,
                           const Workspace& ws, uint32_t* counts, uint32_t* mask_out, hipStream_t st,
                           hipEvent_t ev_start, hipEvent_t ev_stop) {
@@ -2531,18 +2545,23 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
     const float scale = 1.0f / sqrtf((float)d);
     if (s.dtype == kBF16) {
         const int nj = routing ? (s.NC * kChunk > s.NK ? s.NC * kChunk : s.NK) : s.NK;
+        const uint16_t* qq = static_cast<const uint16_t*>(q);
         const uint16_t* kk = static_cast<const uint16_t*>(k);
         const uint16_t* vv = static_cast<const uint16_t*>(v);
+        const dim3 grid(nj + (routing ? s.NQ : 0), s.BH);
+        const uint32_t count0 = routing ? 0u : dense_count(s);
         if (d == 128)
-            prep_kv_kernel<128><<<dim3(nj, s.BH), dim3(256), 0, st>>>(kk, vv, ws.kbar, ws.kbarh, ws.vbarh, ws.vt, s.N,
-                                                                      s.NK, s.NKr, s.NC, routing ? 1 : 0);
+            prep_kernel<128><<<grid, dim3(256), 0, st>>>(kk, vv, ws.kbar, ws.kbarh, ws.vbarh, ws.vt, s.N, s.NK, s.NKr,
+                                                         s.NC, routing ? 1 : 0, qq, ws.qbar, s.bq, s.NQ, nj, ws.queue,
+                                                         counts, count0);
         else
-            prep_kv_kernel<64><<<dim3(nj, s.BH), dim3(256), 0, st>>>(kk, vv, ws.kbar, ws.kbarh, ws.vbarh, ws.vt, s.N,
-                                                                     s.NK, s.NKr, s.NC, routing ? 1 : 0);
+            prep_kernel<64><<<grid, dim3(256), 0, st>>>(kk, vv, ws.kbar, ws.kbarh, ws.vbarh, ws.vt, s.N, s.NK, s.NKr,
+                                                        s.NC, routing ? 1 : 0, qq, ws.qbar, s.bq, s.NQ, nj, ws.queue,
+                                                        counts, count0);
         if ((e = hipGetLastError()) != hipSuccess) return e;
+        const bool direct = routing && direct_stats(s);
         if (routing) {
-            if ((e = launch_pool_mean(q, ws.qbar, kBF16, s.BH, s.N, d, s.bq, st)) != hipSuccess) return e;
-            if (!s.causal) {   // causal masks: the kernel takes each row's statistics itself
+            if (!s.causal && !direct) {   // causal masks: the kernel takes each row's statistics itself
                 if ((e = launch_moments(ws.kbar, ws.muk, ws.cov, ws.mom, s.BH, s.NK, s.NKr, d, st)) != hipSuccess)
                     return e;
                 if ((e = launch_tau(ws.qbar, ws.muk, ws.cov, ws.tau, nullptr, ws.sigma, s.BH, s.NQ, d, beta, s.diag,
@@ -2552,18 +2571,18 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
             }
         }
         AttnArgs a{};
-        a.order = (routing && !s.causal) ? ws.order : nullptr;
+        a.order = (routing && !s.causal && !direct) ? ws.order : nullptr;
         a.queue = ws.queue;
-        a.q = static_cast<const uint16_t*>(q);
+        a.q = qq;
         a.k = kk;
         a.vt = ws.vt;
         a.qbar = ws.qbar;
         a.kbar = ws.kbar;
         a.kbarh = ws.kbarh;
         a.vbarh = ws.vbarh;
-        a.tau = ws.tau;
+        a.tau = direct ? nullptr : ws.tau;
         a.out = static_cast<uint16_t*>(out);
-        a.blkcount = ws.blkcount;
+        a.counts = counts;
         a.mask_out = mask_out;
         a.BH = s.BH; a.N = s.N; a.NQ = s.NQ; a.NK = s.NK; a.NKr = s.NKr; a.NC = s.NC; a.MW = s.MW;
         a.hlog = s.causal ? 0 : heads_in_flight_log2(s);
@@ -2574,8 +2593,6 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.c_log2 = scale * kLog2e;
         a.bias_full = log2f((float)kBlockK) / a.c_log2;
         a.bias_last = log2f((float)(s.N - (s.NK - 1) * kBlockK)) / a.c_log2;
-        queue_reset_kernel<<<1, 64, 0, st>>>(ws.queue);   // a fill kernel, not a memset: safe under graph capture
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         if (ev_start && (e = hipEventRecord(ev_start, st)) != hipSuccess) return e;
         if (d == 128) e = s.bq == 128 ? dispatch_bf16<128, 128>(s, a, st) : dispatch_bf16<128, 64>(s, a, st);
         else e = s.bq == 128 ? dispatch_bf16<64, 128>(s, a, st) : dispatch_bf16<64, 64>(s, a, st);
@@ -2625,10 +2642,8 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         else e = s.bq == 128 ? dispatch_f32<64, 128>(s, a, st) : dispatch_f32<64, 64>(s, a, st);
         if (e != hipSuccess) return e;
         if (ev_stop && (e = hipEventRecord(ev_stop, st)) != hipSuccess) return e;
-        return hipSuccess;
     }
-    count_reduce_kernel<<<dim3(s.BH), dim3(256), 0, st>>>(ws.blkcount, counts, s.NQ);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace sol
