@@ -101,9 +101,9 @@ int sol_attn_pool_blocks(const void* q, const void* k, const void* v,
  * qbar: [B,H,NQ,d] f32 device; kbar: [B,H,NK,d] f32 device (NK >= nk_routable,
  * row stride d, NK rows per (b,h)).  tau (required), mu, sigma (optional):
  * [B,H,NQ] f32 device.  beta must not be NaN.  threshold_mode: 0 (exact) or
- * SOL_THRESHOLD_DIAGONAL.  Unlike the forward calls this entry point allocates
- * temporary device memory for the moments and synchronises `stream` before
- * returning.
+ * SOL_THRESHOLD_DIAGONAL.  Unlike the forward calls this entry point synchronises
+ * `stream` before returning.  The moments' scratch memory is the library's: up
+ * to 96 MiB per device are kept until sol_attn_release, more is freed at once.
  */
 int sol_attn_thresholds(const float* qbar, const float* kbar,
                         float* tau, float* mu, float* sigma,

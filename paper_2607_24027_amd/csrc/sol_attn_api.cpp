@@ -47,6 +47,17 @@ struct DeviceBuffers {
 std::mutex g_mu;
 std::map<int, DeviceBuffers> g_bufs;
 
+// Moment scratch of sol_attn_thresholds, one buffer per device, grown on demand up to kMaxMomentBytes and given back by
+// sol_attn_release; larger ones live for one call.  The mutex is held from the launches to the end of the
+// call's synchronisation, so no two calls share the buffer.
+std::mutex g_mom_mu;
+struct MomentBuffer {
+    void* p = nullptr;
+    size_t bytes = 0;
+};
+std::map<int, MomentBuffer> g_mom;
+constexpr size_t kMaxMomentBytes = (size_t)96 << 20;
+
 // What sol_attn_stats needs to turn a counts buffer into fractions: one record per counts
 // buffer a forward wrote (keyed by its device address), with an event recorded on the
 // forward's stream right after the counts were written.  Waiting on the event instead of the
@@ -134,11 +145,8 @@ int sol_attn_pool_blocks(const void* q, const void* k, const void* v, float* qba
     if ((qbar && !q) || (kbar && !k) || (vbar && !v))
         return fail(SOL_ERR_INVALID_ARG, "an input matching a non-null output is null");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int BH = B * H;
-    hipError_t e;
-    if (qbar && (e = sol::launch_pool_mean(q, qbar, dtype, BH, N, d, block_q, st)) != hipSuccess) return hip_fail(e, "pool q");
-    if (kbar && (e = sol::launch_pool_mean(k, kbar, dtype, BH, N, d, block_k, st)) != hipSuccess) return hip_fail(e, "pool k");
-    if (vbar && (e = sol::launch_pool_mean(v, vbar, dtype, BH, N, d, block_k, st)) != hipSuccess) return hip_fail(e, "pool v");
+    const hipError_t e = sol::launch_pool(q, k, v, qbar, kbar, vbar, nullptr, dtype, B * H, N, d, block_q, block_k, st);
+    if (e != hipSuccess) return hip_fail(e, "pooling");
     return ok();
 }
 
@@ -153,11 +161,22 @@ int sol_attn_thresholds(const float* qbar, const float* kbar, float* tau, float*
         return fail(SOL_ERR_INVALID_ARG, "threshold_mode must be 0 or SOL_THRESHOLD_DIAGONAL (got %d)", threshold_mode);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int BH = B * H;
-    // Moment buffers are temporary: allocate, run, wait, free (this entry point synchronises).
-    void* mom = nullptr;
     const size_t part = sol::moments_scratch_bytes(BH, nk_routable, d);
-    hipError_t e = hipMalloc(&mom, part + ((size_t)BH * d * d + (size_t)BH * d) * sizeof(float));
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(moments)");
+    const size_t need = part + ((size_t)BH * d * d + (size_t)BH * d) * sizeof(float);
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    std::lock_guard<std::mutex> lock(g_mom_mu);
+    MomentBuffer& buf = g_mom[dev];
+    void* mom = buf.p;
+    if (buf.bytes < need) {
+        e = hipMalloc(&mom, need);
+        if (e != hipSuccess) return hip_fail(e, "hipMalloc(moments)");
+        if (need <= kMaxMomentBytes) {
+            if (buf.p) (void)hipFree(buf.p);   // idle: every call waits for its kernels
+            buf = MomentBuffer{mom, need};
+        }
+    }
     double* scratch = static_cast<double*>(mom);
     float* cov = reinterpret_cast<float*>(static_cast<char*>(mom) + part);
     float* muk = cov + (size_t)BH * d * d;
@@ -165,7 +184,7 @@ int sol_attn_thresholds(const float* qbar, const float* kbar, float* tau, float*
     if (e == hipSuccess) e = sol::launch_tau(qbar, muk, cov, tau, mu, sigma, BH, NQ, d, beta,
                                                     threshold_mode == SOL_THRESHOLD_DIAGONAL ? 1 : 0, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    (void)hipFree(mom);
+    if (mom != buf.p) (void)hipFree(mom);
     if (e != hipSuccess) return hip_fail(e, "threshold kernels");
     return ok();
 }
@@ -459,8 +478,14 @@ int sol_attn_kernel_timing(float* total_ms, int* launches) {
 
 int sol_attn_release(void) {
     std::lock_guard<std::mutex> lock(g_mu);
+    std::lock_guard<std::mutex> mom_lock(g_mom_mu);
     int cur = 0;
     (void)hipGetDevice(&cur);
+    for (auto& kv : g_mom) {
+        (void)hipSetDevice(kv.first);
+        if (kv.second.p) (void)hipFree(kv.second.p);
+    }
+    g_mom.clear();
     for (auto& kv : g_bufs) {
         (void)hipSetDevice(kv.first);
         (void)hipDeviceSynchronize();

@@ -74,8 +74,9 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws);
 // Dynamic LDS bytes of the fused attention kernel for this shape.
 size_t attn_lds_bytes(const Shape& s);
 
-hipError_t launch_pool_mean(const void* x, float* mean, int dtype, int BH, int N, int d, int blk,
-                            hipStream_t st);
+// Block means of q (blocks of bq), k and v (blocks of bk); an output may be null.  counts (or null) are cleared.
+hipError_t launch_pool(const void* q, const void* k, const void* v, float* qbar, float* kbar, float* vbar,
+                       uint32_t* counts, int dtype, int BH, int N, int d, int bq, int bk, hipStream_t st);
 size_t moments_scratch_bytes(int BH, int NKr, int d);
 hipError_t launch_moments_final(const float* kbar, float* muk, float* cov, double* scratch, int BH, int NK, int NKr,
                                 int d, hipStream_t st);

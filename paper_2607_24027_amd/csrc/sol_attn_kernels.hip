@@ -129,30 +129,24 @@ __device__ __forceinline__ void pool_mean_block(const T* __restrict__ x, float* 
     }
 }
 
+// Block means of up to three tensors in one launch: grid (blocks of q, then of k, then of v; BH), a tensor without
+// an output has no blocks.  counts, when given, are cleared (the f32 forward, whose pre-pass this is).
 template <typename T>
-__global__ __launch_bounds__(256) void pool_mean_kernel(const T* __restrict__ x, float* __restrict__ mean,
-                                                        int N, int D, int blk, int nb) {
+__global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
+                                                   const T* __restrict__ v, float* __restrict__ qbar,
+                                                   float* __restrict__ kbar, float* __restrict__ vbar,
+                                                   uint32_t* __restrict__ counts, int N, int D, int bq, int bk, int nbq,
+                                                   int nbk, int nq, int nk) {
     __shared__ float red[256 * Elem<T>::kPerChunk];
-    pool_mean_block<T>(x, mean, N, D, blk, nb, blockIdx.x, blockIdx.y, red);
-}
-
-// The f32 forward's pooling in one launch: grid (NQ + NK [+ NK], BH), the query blocks, then the key
-// blocks, then (sparse mode) the value blocks; it also clears the head's count of selected pairs.
-__global__ __launch_bounds__(256) void prep_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                       const float* __restrict__ v, float* __restrict__ qbar,
-                                                       float* __restrict__ kbar, float* __restrict__ vbar,
-                                                       uint32_t* __restrict__ counts, int N, int D, int bq, int NQ,
-                                                       int NK) {
-    __shared__ float red[256 * Elem<float>::kPerChunk];
     const int bh = blockIdx.y;
     int j = blockIdx.x;
-    if (j == 0 && threadIdx.x == 0) counts[bh] = 0u;
-    const bool isq = j < NQ;
-    if (!isq) j -= NQ;
-    const bool isv = !isq && j >= NK;
-    if (isv) j -= NK;
-    pool_mean_block<float>(isq ? q : isv ? v : k, isq ? qbar : isv ? vbar : kbar, N, D, isq ? bq : kBlockK,
-                           isq ? NQ : NK, j, bh, red);
+    if (counts && j == 0 && threadIdx.x == 0) counts[bh] = 0u;
+    const bool isq = j < nq;
+    if (!isq) j -= nq;
+    const bool isv = !isq && j >= nk;
+    if (isv) j -= nk;
+    pool_mean_block<T>(isq ? q : isv ? v : k, isq ? qbar : isv ? vbar : kbar, N, D, isq ? bq : bk, isq ? nbq : nbk, j, bh,
+                       red);
 }
 
 // ---------------------------------------------------------------------------
@@ -2491,12 +2485,19 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
     return off;
 }
 
-hipError_t launch_pool_mean(const void* x, float* mean, int dtype, int BH, int N, int d, int blk, hipStream_t st) {
-    const int nb = (N + blk - 1) / blk;
+hipError_t launch_pool(const void* q, const void* k, const void* v, float* qbar, float* kbar, float* vbar,
+                       uint32_t* counts, int dtype, int BH, int N, int d, int bq, int bk, hipStream_t st) {
+    const int nbq = (N + bq - 1) / bq, nbk = (N + bk - 1) / bk;
+    const int nq = qbar ? nbq : 0, nk = kbar ? nbk : 0, nv = vbar ? nbk : 0;
+    const dim3 grid(nq + nk + nv, BH);
     if (dtype == kBF16)
-        pool_mean_kernel<uint16_t><<<dim3(nb, BH), dim3(256), 0, st>>>(static_cast<const uint16_t*>(x), mean, N, d, blk, nb);
+        pool_kernel<uint16_t><<<grid, dim3(256), 0, st>>>(
+            static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), qbar, kbar,
+            vbar, counts, N, d, bq, bk, nbq, nbk, nq, nk);
     else
-        pool_mean_kernel<float><<<dim3(nb, BH), dim3(256), 0, st>>>(static_cast<const float*>(x), mean, N, d, blk, nb);
+        pool_kernel<float><<<grid, dim3(256), 0, st>>>(static_cast<const float*>(q), static_cast<const float*>(k),
+                                                       static_cast<const float*>(v), qbar, kbar, vbar, counts, N, d, bq,
+                                                       bk, nbq, nbk, nq, nk);
     return hipGetLastError();
 }
 
@@ -2663,10 +2664,9 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         // moments; so do proxy rows past kF32ProxMax, which would not leave room for two workgroups a CU.
         const bool moments = routing && !s.causal && (s.diag || s.NKr > kF32ProxMax);
         if (routing) {
-            prep_f32_kernel<<<dim3(s.NQ + (s.mode == kSparse ? 2 : 1) * s.NK, s.BH), dim3(256), 0, st>>>(
-                static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v), ws.qbar,
-                ws.kbar, ws.vbar, counts, s.N, d, s.bq, s.NQ, s.NK);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
+            e = launch_pool(q, k, v, ws.qbar, ws.kbar, s.mode == kSparse ? ws.vbar : nullptr, counts, kF32, s.BH, s.N, d,
+                            s.bq, s.bk, st);
+            if (e != hipSuccess) return e;
             if (moments) {
                 if ((e = launch_moments(ws.kbar, ws.muk, ws.cov, ws.mom, s.BH, s.NK, s.NKr, d, st)) != hipSuccess)
                     return e;
