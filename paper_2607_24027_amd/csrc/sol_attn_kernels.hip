@@ -1061,7 +1061,12 @@ constexpr bool kAttnKeySplit = (D == 128 && BQ == 64);
 template <int D, int BQ>
 constexpr int kAttnThreads = kAttnKeySplit<D, BQ> ? 256 : BQ * 2;
 
-// Every instantiation is register-budgeted for two waves per SIMD.
+// Waves per SIMD that the registers are budgeted for.  d = 64 with 128-row blocks: three (168 registers; a tile has half
+// the MFMAs for the same softmax work, so a third wave has more to fill: 24 heads of 10,865 tokens sparse 313 -> 289 us,
+// with four and their spills 296); with 64-row blocks (two waves a workgroup) LDS holds four workgroups a CU, two
+// waves.
+template <int D, int BQ>
+constexpr int kAttnWaves = D == 64 && BQ == 128 ? 3 : 2;
 // One query block (b, h, qi) of the fused kernel; y is its position in its XCD's queue.
 template <int D, int BQ, int MODE, bool CAUSAL>
 __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const int bh, const int qi, const int y) {
@@ -1553,29 +1558,10 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
         // max of tile t+1 (finishing QK^T(t+1) early measured 1-2% faster than interleaving it
         // with PV(t)).  Successive MFMAs on one accumulator are at least two slots apart, and
         // operands are read from LDS two slots ahead.  Under the key split the same schedule has
-        // 8 + 8 slots (one 32-key score tile, two P blocks).
-        // Generic iteration (any D): the same work in source order.
-        auto step_generic = [&](auto par_tag, int t) SOL_INLINE {
-            constexpr int P = decltype(par_tag)::value;
-            rescale(mx);
-            if (t + 2 < T) issue_k(ck, P);
-            issue_v(cv, P ^ 1);
-            const int cn = t + 3 < T ? code(t + 3) : 0;
-            f32x16 n0 = f32x16{}, n1 = f32x16{};
-            qk(apx_tag, std::integral_constant<int, P ^ 1>{}, qop, n0, n1);
-            f16x8 pb[NPB];
-            exps(s0, s1, pb, bo);
-            pv(apx_tag, par_tag, pb);
-            bo = scores_done(t + 1, cv, n0, n1);
-            mx = tile_max_l2(n0, n1, bo);
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            s0 = n0;
-            s1 = n1;
-            cv = ck;
-            ck = cn;
-        };
-        auto step_slots = [&](auto par_tag, int t) SOL_INLINE {
+        // 8 + 8 slots (one 32-key score tile, two P blocks), and at d = 64 8 + 8 slots with two
+        // pairs of exponentials beside each QK^T MFMA (4-5 % faster there than the same work in
+        // source order: sparse 289 -> 275, dense 802 -> 747 us at 24 heads of 10,865 tokens).
+        auto step = [&](auto par_tag, int t) SOL_INLINE {
             constexpr int P = decltype(par_tag)::value;
             constexpr int KOFF = (P ^ 1) * L::STAGE;   // K of tile t+1
             constexpr int VOFF = P * L::STAGE;         // V of tile t
@@ -1606,6 +1592,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
             // rest PV (index i: k-step i/4, d M-tile i%4).  Under the key split a wave has 8 + 8
             // slots, each of the first 8 with one exponential pair.
             constexpr int NQK = NKS * NS, NSLOT = NQK + NPB * NDT;
+            constexpr int EPS = 4 * NPB / NQK;   // exponential pairs per QK^T slot (d = 64: two)
             auto kind = [](int sl) SOL_INLINE { return sl < NQK ? 0 : 1; };
             auto index = [](int sl) SOL_INLINE { return sl < NQK ? sl : sl - NQK; };
             auto ldk = [&](int qi) SOL_INLINE {
@@ -1613,8 +1600,8 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
                 else return *reinterpret_cast<const KT*>(smem + kadr[qi >> 1] + KOFF + (qi & 1) * KT1);
             };
             auto ldv = [&](int pi) SOL_INLINE -> f16x8 {
-                if constexpr (APX) return ldv_apx(pi >> 2, pi & 3, VOFF);
-                else return *reinterpret_cast<const f16x8*>(smem + vadr[pi >> 2] + VOFF + (pi & 3) * VMT);
+                if constexpr (APX) return ldv_apx(pi / NDT, pi % NDT, VOFF);
+                else return *reinterpret_cast<const f16x8*>(smem + vadr[pi / NDT] + VOFF + (pi % NDT) * VMT);
             };
             KT kop[4];
             f16x8 vop[4];
@@ -1646,9 +1633,12 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
                     else n0 = mfma_qk(av, qop[id >> 1], n0);
                 } else {
                     const f16x8 av = vop[(uv++) & 3];
-                    o[id & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, pb[id >> 2], o[id & 3], 0, 0, 0);
+                    o[id % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, pb[id / NDT], o[id % NDT], 0, 0, 0);
                 }
-                if (sl < 4 * NPB) exp_pair(sl >> 2, sl & 3);
+                if (sl < NQK) {
+#pragma unroll
+                    for (int e = 0; e < EPS; ++e) exp_pair((sl * EPS + e) >> 2, (sl * EPS + e) & 3);
+                }
                 // row max of tile t+1 in the second-last slot (0.2-0.8% faster than after the last;
                 // the causal kernels take it after the loop: their masked form inside the
                 // unrolled loop multiplies the code)
@@ -1659,9 +1649,12 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
                     }
                 }
                 if constexpr (kRowSumInPV) {
-                    if (sl >= NQK && sl - NQK < 4 * NPB) {   // pair sl - NQK, while its P block is read
-                        const int kk = (sl - NQK) >> 2, q = (sl - NQK) & 3;
-                        l_run[kk] = add_f16x2(l_run[kk], f16x2{pb[kk][2 * q], pb[kk][2 * q + 1]});
+                    if (sl >= NQK) {   // the pairs of slot sl - NQK, about when their P block is read
+#pragma unroll
+                        for (int e = 0; e < EPS; ++e) {
+                            const int kk = ((sl - NQK) * EPS + e) >> 2, q = ((sl - NQK) * EPS + e) & 3;
+                            l_run[kk] = add_f16x2(l_run[kk], f16x2{pb[kk][2 * q], pb[kk][2 * q + 1]});
+                        }
                     }
                 }
                 // Each slot is its own scheduling region: left free, the scheduler sinks the
@@ -1679,10 +1672,6 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
             s1 = n1;
             cv = ck;
             ck = cn;
-        };
-        auto step = [&](auto par_tag, int t) SOL_INLINE {
-            if constexpr (D == 128) step_slots(par_tag, t);
-            else step_generic(par_tag, t);
         };
         int t = 0;
         for (; t + 2 < T; t += 2) {
@@ -1816,7 +1805,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
 // which workgroup computes it, and every claim either takes a block or finds a queue empty
 // for good, so each workgroup stops after at most eight failed claims.
 template <int D, int BQ, int MODE, bool CAUSAL>
-__global__ __launch_bounds__((kAttnThreads<D, BQ>)) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__((kAttnThreads<D, BQ>)) __attribute__((amdgpu_waves_per_eu(kAttnWaves<D, BQ>, kAttnWaves<D, BQ>)))
 void routed_attn_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ int s_task[2];
@@ -2306,7 +2295,10 @@ hipError_t allow_lds(K kernel, size_t bytes) {
 
 template <int D, int BQ, int MODE, bool CAUSAL>
 hipError_t launch_attn_bf16(const Shape& s, const AttnArgs& a, hipStream_t st) {
-    const size_t lds = attn_lds_bytes(s);
+    size_t lds = attn_lds_bytes(s);
+    // Few causal blocks (at most four a CU): two workgroups a CU although three fit.  With three, the CUs that get
+    // three long blocks finish last (16 heads of 4,097 tokens, d = 64, dense: 111 against 83 us).
+    if (CAUSAL && kAttnWaves<D, BQ> > 2 && (long long)a.BH * a.NQ <= 1024) lds = std::max(lds, (size_t)kMaxLds / 3 + 1024);
     auto kern = routed_attn_kernel<D, BQ, MODE, CAUSAL>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
