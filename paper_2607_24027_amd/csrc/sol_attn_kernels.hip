@@ -957,6 +957,7 @@ struct AttnArgs {
     float scale, c_log2;
     float bias_full, bias_last;   // log2(n_j)/c_log2 for full blocks and for the last block
     int causal_g;                 // causal granule G (CAUSAL kernels): key s visible to query t iff s < lim(t)
+    int snake;                    // causal queue order: 0 head by head in segments, 1 block by block over all heads
     float beta;                   // standardised cutoff (CAUSAL kernels take tau_i on chip)
 };
 
@@ -1798,7 +1799,9 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
 // sparse modes), so the workgroups resident on one XCD work through neighbouring blocks of one
 // head and share its K/V in their L2.  Under a causal mask the work of a query block grows with its index, so the
 // head's blocks are cut into 16 segments and queue x takes segment 15 - x (descending, the
-// longer blocks first) and then segment x.  Consecutive workgroups go round-robin to the 8
+// longer blocks first) and then segment x, head by head; short heads (AttnArgs::snake) are instead dealt to the
+// queues block by block, to and fro, the longest blocks of all heads first: 16 segments of a few blocks
+// do not come out even, and a long block that starts late ends late.  Consecutive workgroups go round-robin to the 8
 // XCDs, so workgroup w serves queue w & 7 first; once that queue is empty it takes blocks
 // from the queue with the most left.  XCDs whose blocks need more tiles, or that run slower,
 // thus get help at the end instead of finishing last.  A block's result does not depend on
@@ -1850,9 +1853,15 @@ void routed_attn_kernel(AttnArgs a) {
         if (x < 0) return;
         int bh, qi;
         if constexpr (CAUSAL) {
-            bh = y / a.per_x;
-            const int u = y % a.per_x, hp = a.per_x >> 1;
-            qi = u < hp ? (15 - x) * hp + (hp - 1 - u) : x * hp + (u - hp);
+            if (a.snake) {
+                const int u = y / a.BH;
+                bh = y % a.BH;
+                qi = a.NQ - 1 - (8 * u + ((u & 1) ? 7 - x : x));
+            } else {
+                bh = y / a.per_x;
+                const int u = y % a.per_x, hp = a.per_x >> 1;
+                qi = u < hp ? (15 - x) * hp + (hp - 1 - u) : x * hp + (u - hp);
+            }
         } else {
             // 2^hlog heads at a time, each on 8 >> hlog XCDs: queue x serves head (x >> gl) of
             // the current group, blocks (x mod 2^gl)*per_x ..
@@ -1861,7 +1870,7 @@ void routed_attn_kernel(AttnArgs a) {
             qi = (x & ((1 << gl) - 1)) * a.per_x + (y % a.per_x);
             if (a.order != nullptr && bh < a.BH && qi < a.NQ) qi = a.order[(size_t)bh * a.NQ + qi];
         }
-        if (bh < a.BH && qi < a.NQ) attn_block<D, BQ, MODE, CAUSAL>(a, smem, bh, qi, y);
+        if (bh < a.BH && qi >= 0 && qi < a.NQ) attn_block<D, BQ, MODE, CAUSAL>(a, smem, bh, qi, y);
     }
 }
 
@@ -2638,7 +2647,13 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.mask_out = mask_out;
         a.BH = s.BH; a.N = s.N; a.NQ = s.NQ; a.NK = s.NK; a.NKr = s.NKr; a.NC = s.NC; a.MW = s.MW;
         a.hlog = s.causal ? 0 : heads_in_flight_log2(s);
-        a.per_x = s.causal ? 2 * ((s.NQ + 15) / 16) : (s.NQ + (8 >> a.hlog) - 1) / (8 >> a.hlog);
+        // Causal launches of at most three rounds of two workgroups a CU: the end of the launch counts for more than one
+        // XCD staying with one head.  Measured, block by block against head by head: 16 heads x 33 blocks (dense)
+        // 84 -> 79 us at d = 64, 125 -> 109 at d = 128; 12 x 110 (dense) 674 -> 604; 4 x 256 1,120 -> 997; 2 x 591
+        // 3,190 -> 2,550; but 24 x 146 2,070 -> 2,157, 24 x 256 5,940 -> 6,510.
+        a.snake = s.causal && (long long)s.BH * s.NQ <= 1536;
+        a.per_x = a.snake ? (s.NQ + 7) / 8
+                  : s.causal ? 2 * ((s.NQ + 15) / 16) : (s.NQ + (8 >> a.hlog) - 1) / (8 >> a.hlog);
         a.scale = scale;
         a.causal_g = s.causal;
         a.beta = beta;
