@@ -546,13 +546,36 @@ __global__ __launch_bounds__(256) void tau_kernel(const float* __restrict__ qbar
 // tau_i = mu_i + beta sigma_i, and the selection bits follow.
 // ---------------------------------------------------------------------------
 
+// One lane's value moved over the wave by the VALU's data-parallel primitives (rows of 16 lanes); lanes without a source
+// or outside ROWS get 0.  A shuffle through the LDS crossbar takes 50 to 100 cycles, and the reductions and
+// scans of the routing prologue were chains of six (short calls 25.7 -> 25.3 us, f32 31.4 -> 30.8, image shape -0.3 %,
+// d = 64 and frame-causal layers -0.5 %, with the mean's sum taken while the proxies are formed).
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp0(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true);
+}
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ float dpp0(float x) {
+    return __int_as_float(dpp0<CTRL, ROWS>(__float_as_int(x)));
+}
+// Inclusive scan over the wave: shifts by 1, 2, 4 and 8 within rows, then the row totals handed on.
+template <typename T>
+__device__ __forceinline__ T wave_scan_incl(T v) {
+    v += dpp0<0x111>(v);
+    v += dpp0<0x112>(v);
+    v += dpp0<0x114>(v);
+    v += dpp0<0x118>(v);
+    v += dpp0<0x142, 0xA>(v);   // lane 15 of rows 0 and 2 to rows 1 and 3
+    v += dpp0<0x143, 0xC>(v);   // lane 31 to rows 2 and 3
+    return v;
+}
+
 // Sum over the workgroup; every thread gets the total.  scratch: NT/64 floats.
 template <int NT>
 __device__ float block_sum(float v, float* scratch) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (lane == 0) scratch[wave] = v;
+    v = wave_scan_incl(v);
+    if (lane == 63) scratch[wave] = v;
     __syncthreads();
     float tot = 0.f;
 #pragma unroll
@@ -565,11 +588,7 @@ template <int NT>
 __device__ int block_scan_incl(int v, int* scratch, int* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int NW = NT / 64;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int y = __shfl_up(v, off);
-        if (lane >= off) v += y;
-    }
+    v = wave_scan_incl(v);
     if (lane == 63) scratch[wave] = v;
     __syncthreads();
     int pre = 0, tot = 0;
@@ -793,6 +812,7 @@ __device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, 
 #pragma unroll
         for (int i = 0; i < CPT; ++i) kv[i] = *reinterpret_cast<const f32x4*>(rp + 4 * (seg + TPK * i));
     };
+    float psum = 0.f;   // sum of the proxies this thread stored (direct)
     auto decide = [&](int c, const f32x4 (&kv)[CPT]) SOL_INLINE {
         float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll
@@ -811,7 +831,10 @@ __device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, 
             dot += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dot), 0x4E, 0xF, 0xF, false));
         const int j = c * kChunk + jl;
         if (direct) {
-            if (seg == 0 && j < nr) prox[j] = scale * dot;
+            if (seg == 0 && j < nr) {
+                prox[j] = scale * dot;
+                psum += scale * dot;
+            }
             return;
         }
         const bool sel = j < nr && scale * dot > tau_i;
@@ -869,16 +892,15 @@ __device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, 
 #pragma unroll
     for (int b = 0; b < NB; ++b)
         if (c + NB + b < NC) decide(c + NB + b, kb[b]);
-    __syncthreads();
+    if (!direct) __syncthreads();
     if (direct) {
-        // row statistics over the routable blocks, then the selection bits of every word
+        // row statistics over the routable blocks, then the selection bits of every word (block_sum's barriers
+        // also put every proxy in LDS before it is read)
         float* fscratch = reinterpret_cast<float*>(scan_scratch);
         float th = -kNegInf;
         if (nr > 0) {
+            const float mu = block_sum<NT>(psum, fscratch) / (float)nr;
             float acc = 0.f;
-            for (int j = tid; j < nr; j += NT) acc += prox[j];
-            const float mu = block_sum<NT>(acc, fscratch) / (float)nr;
-            acc = 0.f;
             for (int j = tid; j < nr; j += NT) {
                 const float dv = prox[j] - mu;
                 acc = fmaf(dv, dv, acc);
