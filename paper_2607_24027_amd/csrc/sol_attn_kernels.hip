@@ -1943,6 +1943,7 @@ struct AttnArgsF32 {
     float scale, c_log2;
     int causal_g;
     int prox_n;               // proxies a row keeps in LDS: NKr with statistics on chip, else 0
+    int aligned;              // k, v and the pooled rows start on 16 bytes (direct copies to LDS)
     float beta;
 };
 
@@ -2105,8 +2106,16 @@ void routed_attn_f32_kernel(AttnArgsF32 a) {
             if (MODE == kSparse && apx) t = ulist[c * kChunk + t];
             off[u] = (uint32_t)(t * RB + cc * 16);
         }
+        if (a.aligned) {
 #pragma unroll
-        for (int u = 0; u < CPW; ++u) lds_copy16(sbase, off[u], (lds_ptr_t)(smem + dst + (wave * CPW + u) * 1024));
+            for (int u = 0; u < CPW; ++u) lds_copy16(sbase, off[u], (lds_ptr_t)(smem + dst + (wave * CPW + u) * 1024));
+        } else {   // tensors that do not start on 16 bytes: dword loads, through registers
+            for (int u = 0; u < CPW; ++u) {
+                const float* x = reinterpret_cast<const float*>(reinterpret_cast<const char*>(sbase) + off[u]);
+                const f32x4 v = {x[0], x[1], x[2], x[3]};
+                *reinterpret_cast<f32x4*>(smem + dst + ((wave * CPW + u) * 64 + ln) * 16) = v;
+            }
+        }
     };
     auto landed = [&]() SOL_INLINE {   // this wave's copies have landed, then everyone's
         __builtin_amdgcn_s_waitcnt(0);
@@ -2713,6 +2722,8 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.vbar = ws.vbar;
         a.tau = moments ? ws.tau : nullptr;
         a.prox_n = routing && !moments ? s.NKr : 0;
+        a.aligned = ((reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v) |
+                      reinterpret_cast<uintptr_t>(ws.kbar) | reinterpret_cast<uintptr_t>(ws.vbar)) & 15) == 0;
         a.out = static_cast<float*>(out);
         a.part = ws.part;
         a.part_ml = ws.part_ml;

@@ -84,3 +84,20 @@ def test_f32_long_rows_take_the_moment_thresholds(dev):
     tau = s_hat.mean(-1) + 1.5 * s_hat.std(-1)
     assert_mask_matches(gmask, s_hat > tau[..., None], s_hat, tau)
     assert_output_close(to_np(out), ref["out"], "f32", "long")
+
+
+@pytest.mark.parametrize("mode,g,d,bq", [("dense", 0, 64, 64), ("sparse", 0, 128, 128), ("sparse", 1, 64, 128)])
+def test_f32_tensors_off_16_bytes(dev, mode, g, d, bq):
+    # views that start 4 bytes into an allocation: the same results as aligned tensors, bit for bit
+    w = small_workload("f32off", (601,), d, bq, dtype="f32", H=2, seed=4)
+    aligned = [t.to(dev) for t in synth.make_qkv(w)]
+    off = []
+    for t in aligned:
+        buf = torch.empty(t.numel() + 1, device=dev)
+        off.append(buf[1:].view(t.shape))
+        off[-1].copy_(t)
+        assert off[-1].data_ptr() % 16 == 4
+    out = torch.empty(aligned[0].numel() + 1, device=dev)[1:].view(aligned[0].shape)
+    ref = sb.forward(*aligned, bq, 64, 0.5, mode, causal_granule=g)
+    sb.forward(*off, bq, 64, 0.5, mode, causal_granule=g, out=out)
+    assert torch.equal(out, ref)
