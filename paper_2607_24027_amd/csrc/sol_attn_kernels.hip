@@ -9,7 +9,7 @@
 //                                                                       threshold_stats_exact)
 //   3b. order         order of each head's query blocks in the attention kernel's work queues
 //                     (scheduling: blocks with similar selections share an L2)
-//                     2 to 3b only for long heads and the diagonal estimator (direct_stats)
+//                     2 to 3b in the routing modes without a causal mask
 //   4. routed_attn    persistent workgroups claim (b, h, query block) items from per-XCD
 //                     queues; per block: route every key block on chip from f32 proxies, then
 //                     one online-softmax pass over correction tiles (pooled keys, Section 3.2
@@ -538,12 +538,15 @@ __global__ __launch_bounds__(256) void tau_kernel(const float* __restrict__ qbar
 // receives the number of unselected routable blocks and *nsel of selected ones.
 //
 // The routable blocks are [0, nr) and the forced ones [nr, ne): without a causal mask
-// nr = NKr and ne = NK (the forced tail).  With a causal mask [0, nr) are the key blocks every row
-// of the query block sees and [nr, ne) those only some rows see.  With `direct` (causal masks:
-// prefix moments of the pooled keys would need a d x d matrix per query block; and callers without
-// a thresholds launch) the row statistics are taken here, from the proxies themselves: the proxies
-// go to LDS (prox, nr floats), their mean and population deviation over [0, nr) give
-// tau_i = mu_i + beta sigma_i, and the selection bits follow.
+// nr = NKr and ne = NK (the forced tail), and tau_i comes from the moments of the pooled keys.  With a
+// causal mask (CAUSAL) [0, nr) are the key blocks every row of the query block sees and [nr, ne) those
+// only some rows see; the row statistics then cover [0, nr) only and are taken here, from the proxies
+// themselves: the proxies go to LDS (prox, nr floats), their mean and population deviation give
+// tau_i = mu_i + beta sigma_i, and the selection bits follow.  (Prefix moments of the pooled keys would
+// need a d x d matrix per query block.)  Without a mask the moments stay the only source of tau, for every
+// size: statistics of the f32 proxies are 20 to 35 us faster in short calls, but a key block
+// whose proxy lies within rounding of tau_i is then selected by one arithmetic and not by the other, and
+// the forward no longer selects by the tau that the thresholds entry point returns.
 // ---------------------------------------------------------------------------
 
 // One lane's value moved over the wave by the VALU's data-parallel primitives (rows of 16 lanes); lanes without a source
@@ -786,8 +789,8 @@ __global__ __launch_bounds__(256) void order_kernel(const float* __restrict__ qb
         if (r < nmine) ord[rank[r]] = (uint16_t)(t + NT * r);
 }
 
-template <int D, int NT, int MODE>
-__device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, const float* __restrict__ kbar_h, bool direct,
+template <int D, int NT, int MODE, bool CAUSAL>
+__device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, const float* __restrict__ kbar_h,
                               float tau_i, float beta, float scale, int nr, int ne, int MW, float* prox,
                               uint32_t* selw, uint16_t* list, int ucap, int* scan_scratch, int* wpre, int* nuns,
                               int* nsel) {
@@ -812,7 +815,7 @@ __device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, 
 #pragma unroll
         for (int i = 0; i < CPT; ++i) kv[i] = *reinterpret_cast<const f32x4*>(rp + 4 * (seg + TPK * i));
     };
-    float psum = 0.f;   // sum of the proxies this thread stored (direct)
+    float psum = 0.f;   // sum of the proxies this thread stored (CAUSAL)
     auto decide = [&](int c, const f32x4 (&kv)[CPT]) SOL_INLINE {
         float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll
@@ -830,7 +833,7 @@ __device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, 
         if constexpr (TPK >= 4)
             dot += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dot), 0x4E, 0xF, 0xF, false));
         const int j = c * kChunk + jl;
-        if (direct) {
+        if constexpr (CAUSAL) {
             if (seg == 0 && j < nr) {
                 prox[j] = scale * dot;
                 psum += scale * dot;
@@ -892,8 +895,8 @@ __device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, 
 #pragma unroll
     for (int b = 0; b < NB; ++b)
         if (c + NB + b < NC) decide(c + NB + b, kb[b]);
-    if (!direct) __syncthreads();
-    if (direct) {
+    if constexpr (!CAUSAL) __syncthreads();
+    if constexpr (CAUSAL) {
         // row statistics over the routable blocks, then the selection bits of every word (block_sum's barriers
         // also put every proxy in LDS before it is read)
         float* fscratch = reinterpret_cast<float*>(scan_scratch);
@@ -967,11 +970,11 @@ struct AttnArgs {
     const float* kbar;
     const _Float16* kbarh;
     const _Float16* vbarh;
-    const float* tau;             // [BH][NQ], or null: each block takes its statistics from its own proxies
+    const float* tau;             // [BH][NQ] thresholds (no causal mask)
     uint16_t* out;
     uint32_t* counts;             // [BH] selected pairs, added to in the routing modes
     uint32_t* mask_out;
-    const uint16_t* order;        // [BH][NQ] query-block order, or null: identity
+    const uint16_t* order;        // [BH][NQ] query-block order (routing without a causal mask), or null: identity
     uint32_t* queue;              // [8][32] per-XCD claim counters, zero at launch
     int resident;                 // workgroups per XCD in the persistent grid (grid / 8)
     int hlog;                     // log2 of the heads whose blocks are in the queues at once (no causal mask)
@@ -1136,11 +1139,10 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
         ntiles = ne;
         nsel = nr;
     } else {
-        const bool direct = CAUSAL || a.tau == nullptr;
-        const float tau_i = direct ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
-        ntiles = route_and_list<D, NT, MODE>(a.qbar + ((size_t)bh * a.NQ + qi) * D, a.kbar + (size_t)bh * a.NK * D,
-                                             direct, tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
-                                             a.NC * kChunk, scan_scratch, wpre, &nuns, &nsel);
+        const float tau_i = CAUSAL ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
+        ntiles = route_and_list<D, NT, MODE, CAUSAL>(a.qbar + ((size_t)bh * a.NQ + qi) * D, a.kbar + (size_t)bh * a.NK * D,
+                                                     tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
+                                                     a.NC * kChunk, scan_scratch, wpre, &nuns, &nsel);
         if (a.mask_out)
             for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
     }
@@ -1931,7 +1933,7 @@ struct AttnArgsF32 {
     const float* qbar;
     const float* kbar;
     const float* vbar;
-    const float* tau;         // [BH][NQ], or null: each block takes its statistics from its own proxies
+    const float* tau;         // [BH][NQ] thresholds (no causal mask)
     float* out;
     float* part;              // [slot][BQ][D] unnormalised O of the shares past a block's first
     float* part_ml;           // [workgroup][BQ][2] running max (log2 units) and row sum
@@ -1942,15 +1944,13 @@ struct AttnArgsF32 {
     uint32_t dense_count;     // selected pairs of a head in dense mode
     float scale, c_log2;
     int causal_g;
-    int prox_n;               // proxies a row keeps in LDS: NKr with statistics on chip, else 0
+    int prox_n;               // proxies a row keeps in LDS: NKr under a causal mask with routing, else 0
     int aligned;              // k, v and the pooled rows start on 16 bytes (direct copies to LDS)
     float beta;
 };
 
-constexpr int kF32ProxMax = 4096;
-
 // LDS of the f32 kernel: a stage of 64 key rows and one of 64 value rows, scan scratch, selection words, lists,
-// word prefixes, a row's proxies (statistics on chip).
+// word prefixes, a row's proxies (causal masks).
 struct LdsF32 {
     size_t scan, selw, list, wpre, prox, bytes;
     __host__ __device__ LdsF32(int d, int MW, int NC, int NK, int prox_n) {
@@ -2026,11 +2026,10 @@ void routed_attn_f32_kernel(AttnArgsF32 a) {
         if (tid == 0 && qx == 0 && sp == 0) a.counts[bh] = a.dense_count;
     } else {
         __builtin_amdgcn_s_setprio(3);   // a chain of latencies: ahead of the other workgroup's tiles
-        const bool direct = CAUSAL || a.tau == nullptr;
-        const float tau_i = direct ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
-        ntiles = route_and_list<D, NT, MODE>(a.qbar + ((size_t)bh * a.NQ + qi) * D, a.kbar + (size_t)bh * a.NK * D,
-                                             direct, tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
-                                             a.NC * kChunk, scan_scratch, wpre, &nuns, &nsel);
+        const float tau_i = CAUSAL ? 0.f : a.tau[(size_t)bh * a.NQ + qi];
+        ntiles = route_and_list<D, NT, MODE, CAUSAL>(a.qbar + ((size_t)bh * a.NQ + qi) * D, a.kbar + (size_t)bh * a.NK * D,
+                                                     tau_i, a.beta, a.scale, nr, ne, a.MW, prox, selw, list,
+                                                     a.NC * kChunk, scan_scratch, wpre, &nuns, &nsel);
         __builtin_amdgcn_s_setprio(0);
         ntiles = __builtin_amdgcn_readfirstlane(ntiles);   // from LDS, the same in every lane: scalar control flow
         nuns = __builtin_amdgcn_readfirstlane(nuns);
@@ -2615,19 +2614,6 @@ uint32_t dense_count(const Shape& s) {
     return tot;
 }
 
-// Whether the bf16 attention kernel takes each row's statistics from its own proxies, without the moments,
-// thresholds and query-block-order launches (the causal kernels always do; the diagonal estimator
-// needs the moments).  Those four launches cost 35 us in the shortest calls and 80-120 us at 480p and image
-// sizes; what they buy is the query-block order's L2 hits, which grow with a head's blocks.  Whole
-// forwards without them: 17 key blocks a head 60 -> 26 us, 85 x 170 (query x key blocks) 321 -> 293, 264 x 264
-// 3,174 -> 3,103, 256 x 512 1,893 -> 1,848; but 313 x 625 4,750 -> 4,793, 513 x 513 3,761 -> 3,863, 591 x 1182
-// 23,740 -> 24,200 us.
-constexpr long long kDirectMaxPairs = 150000;
-bool direct_stats(const Shape& s) {
-    return !s.causal && !s.diag && (long long)s.NQ * s.NKr <= kDirectMaxPairs &&
-           4 * (long long)s.NKr <= 4LL * kBlockK * s.d * 2;   // the proxies fit in the tile stages
-}
-
 hipError_t launch_forward(const Shape& s, const void* q, const void* k, const void* v, void* out, float beta,
                           const Workspace& ws, uint32_t* counts, uint32_t* mask_out, hipStream_t st,
                           hipEvent_t ev_start, hipEvent_t ev_stop) {
@@ -2651,9 +2637,8 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
                                                         s.NC, routing ? 1 : 0, qq, ws.qbar, s.bq, s.NQ, nj, ws.queue,
                                                         counts, count0);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        const bool direct = routing && direct_stats(s);
         if (routing) {
-            if (!s.causal && !direct) {   // causal masks: the kernel takes each row's statistics itself
+            if (!s.causal) {   // causal masks: the kernel takes each row's statistics itself
                 if ((e = launch_moments(ws.kbar, ws.muk, ws.cov, ws.mom, s.BH, s.NK, s.NKr, d, st)) != hipSuccess)
                     return e;
                 if ((e = launch_tau(ws.qbar, ws.muk, ws.cov, ws.tau, nullptr, ws.sigma, s.BH, s.NQ, d, beta, s.diag,
@@ -2663,7 +2648,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
             }
         }
         AttnArgs a{};
-        a.order = (routing && !s.causal && !direct) ? ws.order : nullptr;
+        a.order = (routing && !s.causal) ? ws.order : nullptr;
         a.queue = ws.queue;
         a.q = qq;
         a.k = kk;
@@ -2672,7 +2657,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.kbar = ws.kbar;
         a.kbarh = ws.kbarh;
         a.vbarh = ws.vbarh;
-        a.tau = direct ? nullptr : ws.tau;
+        a.tau = ws.tau;
         a.out = static_cast<uint16_t*>(out);
         a.counts = counts;
         a.mask_out = mask_out;
@@ -2697,15 +2682,11 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         if (e != hipSuccess) return e;
         if (ev_stop && (e = hipEventRecord(ev_stop, st)) != hipSuccess) return e;
     } else {
-        // Each block takes its statistics from its own proxies (no moments, no thresholds launch): a wave's share
-        // of that is a few thousand cycles against 16,000 for one tile.  The diagonal estimator needs the
-        // moments; so do proxy rows past kF32ProxMax, which would not leave room for two workgroups a CU.
-        const bool moments = routing && !s.causal && (s.diag || s.NKr > kF32ProxMax);
         if (routing) {
             e = launch_pool(q, k, v, ws.qbar, ws.kbar, s.mode == kSparse ? ws.vbar : nullptr, counts, kF32, s.BH, s.N, d,
                             s.bq, s.bk, st);
             if (e != hipSuccess) return e;
-            if (moments) {
+            if (!s.causal) {   // causal masks: the kernel takes each row's statistics itself
                 if ((e = launch_moments(ws.kbar, ws.muk, ws.cov, ws.mom, s.BH, s.NK, s.NKr, d, st)) != hipSuccess)
                     return e;
                 if ((e = launch_tau(ws.qbar, ws.muk, ws.cov, ws.tau, nullptr, nullptr, s.BH, s.NQ, d, beta, s.diag,
@@ -2720,8 +2701,8 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.qbar = ws.qbar;
         a.kbar = ws.kbar;
         a.vbar = ws.vbar;
-        a.tau = moments ? ws.tau : nullptr;
-        a.prox_n = routing && !moments ? s.NKr : 0;
+        a.tau = ws.tau;
+        a.prox_n = routing && s.causal ? s.NKr : 0;
         a.aligned = ((reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v) |
                       reinterpret_cast<uintptr_t>(ws.kbar) | reinterpret_cast<uintptr_t>(ws.vbar)) & 15) == 0;
         a.out = static_cast<float*>(out);

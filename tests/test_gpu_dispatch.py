@@ -1,6 +1,6 @@
-"""bf16 dispatch edges, against the fp64 oracle: shapes on both sides of the line between statistics taken on chip from
-a row's proxies and from the pooled keys' moments (query blocks x key blocks of a head), and causal launches on both
-sides of the line between the two queue orders (query blocks of all heads)."""
+"""bf16 dispatch edges, against the fp64 oracle: heads of few and many (query block, key block) pairs, whose thresholds
+all come from the pooled keys' moments, and causal launches on both sides of the line between the two queue orders
+(query blocks of all heads)."""
 import math
 
 import numpy as np
@@ -23,13 +23,13 @@ def dev():
 
 
 @pytest.mark.parametrize("N,d,bq,text,mode", [
-    (387 * 64, 64, 64, 0, "sparse"),                         # 149,769 pairs: on chip
-    (387 * 64 + 1, 64, 64, 0, "sparse"),                     # 150,544: moments and order, a last block of one row
-    (24640 + 192, 64, 64, 192, "sparse_no_correction"),      # 388 x 385 with a forced tail: on chip
-    (548 * 64 - 5, 128, 128, 0, "sparse"),                   # 274 x 548 = 150,152: moments
+    (387 * 64, 64, 64, 0, "sparse"),                         # 149,769 pairs
+    (387 * 64 + 1, 64, 64, 0, "sparse"),                     # a last block of one row
+    (24640 + 192, 64, 64, 192, "sparse_no_correction"),      # 388 x 385 with a forced tail
+    (548 * 64 - 5, 128, 128, 0, "sparse"),                   # 274 x 548 = 150,152
     (130, 128, 64, 64, "sparse"),                            # two routable blocks, a forced one
 ])
-def test_statistics_on_chip_or_from_moments(dev, N, d, bq, text, mode):
+def test_statistics_from_moments(dev, N, d, bq, text, mode):
     w = small_workload("line", (N - text,), d, bq, text_tokens=text, H=1, seed=N)
     q, k, v = synth.make_qkv(w)
     nkr = w.NK - text // 64
@@ -48,6 +48,45 @@ def test_statistics_on_chip_or_from_moments(dev, N, d, bq, text, mode):
     blocks = sorted({0, w.NQ // 2, w.NQ - 1})
     ref = ora.forward(qn, kn, vn, bq, 64, 0.7, mode, keep_tail_tokens=text, query_blocks=blocks, mask=gmask)["out"]
     assert_output_close(to_np(out), ref, "bf16", mode)
+
+
+def kernel_proxies(qbar, kbar, tpk):
+    """The forward's f32 proxies, operation by operation: a key's row in 16-byte chunks over tpk threads, four fused
+    sums per thread (in 64 bits the products of two f32 are exact, so one rounding per step), then the threads'."""
+    nq, d = qbar.shape
+    nk = kbar.shape[0]
+    qc = qbar.reshape(nq, 1, d // (4 * tpk), tpk, 4).astype(np.float64)
+    kc = kbar.reshape(1, nk, d // (4 * tpk), tpk, 4).astype(np.float64)
+    a = np.zeros((nq, nk, tpk, 4), np.float32)
+    for i in range(d // (4 * tpk)):
+        a = (a.astype(np.float64) + qc[:, :, i] * kc[:, :, i]).astype(np.float32)
+    dot = (a[..., 0] + a[..., 1]) + (a[..., 2] + a[..., 3])
+    while dot.shape[-1] > 1:
+        dot = dot[..., 0::2] + dot[..., 1::2]
+    return np.float32(1.0 / math.sqrt(d)) * dot[..., 0]
+
+
+@pytest.mark.parametrize("dtype,d,bq", [("bf16", 64, 64), ("bf16", 64, 128), ("bf16", 128, 64), ("bf16", 128, 128),
+                                        ("f32", 64, 64), ("f32", 128, 128)])
+def test_forward_selects_by_the_threshold_entry_points_tau(dev, dtype, d, bq):
+    # Two kinds of key block, half of each: at beta = 1 the larger proxy of every row equals tau_i in exact
+    # arithmetic, so rounding alone decides, and only a forward that takes its tau from the same moments
+    # agrees with sol_attn_thresholds on every row.  Tokens of a block are equal: their means are exact.
+    H, nk, tpk = 2, 66, 2 if dtype == "bf16" and d == 64 and bq == 64 else 4
+    g = torch.Generator().manual_seed(d + bq)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    kinds = torch.randn(H, 2, d, generator=g).bfloat16()
+    k = kinds[:, torch.arange(nk) % 2].repeat_interleave(64, dim=1)[None].to(dt)
+    q = torch.randn(1, H, nk * 64 // bq, d, generator=g).bfloat16().repeat_interleave(bq, dim=2).to(dt)
+    q, k, v = (x.contiguous().to(dev) for x in (q, k, torch.randn(k.shape, generator=g).to(dt)))
+    mask = torch.zeros((1, H, q.shape[2] // bq, sb.mask_words(nk)), dtype=torch.int32, device=dev)
+    sb.forward(q, k, v, bq, 64, 1.0, "sparse", mask_out=mask)
+    got = sb.unpack_mask(mask.cpu().numpy().view(np.uint32), nk)
+    qbar, kbar, _ = sb.pool_blocks(q, k, v, bq, 64)
+    tau = sb.thresholds(qbar, kbar, 1.0)[0].cpu().numpy()
+    for h in range(H):
+        s_hat = kernel_proxies(qbar[0, h].cpu().numpy(), kbar[0, h].cpu().numpy(), tpk)
+        assert np.array_equal(got[0, h], s_hat > tau[0, h][:, None])
 
 
 @pytest.mark.parametrize("H,N,d,bq,g,mode", [
