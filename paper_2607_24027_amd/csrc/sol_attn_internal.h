@@ -62,6 +62,7 @@ struct Workspace {
     float* sigma = nullptr;      // [BH][NQ] sigma_i of the thresholds (query-block order)
     uint16_t* order = nullptr;   // [BH][NQ] query-block order of the sparse kernels
     double* mom = nullptr;       // partial moments, moments_scratch_bytes()
+    unsigned long long* tally = nullptr;  // [BH] blocks done << 32 | selected pairs (routing, NQ > 1)
     uint32_t* queue = nullptr;   // [8][32] per-XCD claim counters of the bf16 attention kernel (one per 128 B)
     float* part = nullptr;       // [slot][bq][d] partial outputs of shared query blocks (f32 path)
     float* part_ml = nullptr;    // [workgroup][bq][2] running maxima and row sums
@@ -74,9 +75,9 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws);
 // Dynamic LDS bytes of the fused attention kernel for this shape.
 size_t attn_lds_bytes(const Shape& s);
 
-// Block means of q (blocks of bq), k and v (blocks of bk); an output may be null.  counts (or null) are cleared.
+// Block means of q (blocks of bq), k and v (blocks of bk); an output may be null.  tally (or null) is cleared.
 hipError_t launch_pool(const void* q, const void* k, const void* v, float* qbar, float* kbar, float* vbar,
-                       uint32_t* counts, int dtype, int BH, int N, int d, int bq, int bk, hipStream_t st);
+                       unsigned long long* tally, int dtype, int BH, int N, int d, int bq, int bk, hipStream_t st);
 size_t moments_scratch_bytes(int BH, int NKr, int d);
 hipError_t launch_moments_final(const float* kbar, float* muk, float* cov, double* scratch, int BH, int NK, int NKr,
                                 int d, hipStream_t st);

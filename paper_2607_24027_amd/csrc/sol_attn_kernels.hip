@@ -130,17 +130,17 @@ __device__ __forceinline__ void pool_mean_block(const T* __restrict__ x, float* 
 }
 
 // Block means of up to three tensors in one launch: grid (blocks of q, then of k, then of v; BH), a tensor without
-// an output has no blocks.  counts, when given, are cleared (the f32 forward, whose pre-pass this is).
+// an output has no blocks.  tally, when given, is cleared (the f32 forward, whose pre-pass this is).
 template <typename T>
 __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                    const T* __restrict__ v, float* __restrict__ qbar,
                                                    float* __restrict__ kbar, float* __restrict__ vbar,
-                                                   uint32_t* __restrict__ counts, int N, int D, int bq, int bk, int nbq,
+                                                   unsigned long long* __restrict__ tally, int N, int D, int bq, int bk, int nbq,
                                                    int nbk, int nq, int nk) {
     __shared__ float red[256 * Elem<T>::kPerChunk];
     const int bh = blockIdx.y;
     int j = blockIdx.x;
-    if (counts && j == 0 && threadIdx.x == 0) counts[bh] = 0u;
+    if (tally && j == 0 && threadIdx.x == 0) tally[bh] = 0ull;
     const bool isq = j < nq;
     if (!isq) j -= nq;
     const bool isv = !isq && j >= nk;
@@ -151,10 +151,10 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ q, cons
 
 // ---------------------------------------------------------------------------
 // Pre-pass of the bf16 forward, one launch.  grid (NJ [+ NQ], BH), 256 threads: one key block each, then (routing
-// modes) one query block each, whose means go to qbar; it also sets what the attention kernel
-// adds to: the claim counters and the heads' counts of selected pairs (0, or in dense mode the final
-// value).  As launches of their own the query means, the counter reset and the sum of per-block
-// counts cost about 4 us each in calls of a few hundred tokens.
+// modes) one query block each, whose means go to qbar; it also clears what the attention kernel adds to, all
+// of it in the call's workspace: the claim counters and the heads' tallies (tally_block).  In dense mode it
+// stores the heads' counts, which are known.  As launches of their own the query means, the counter reset and
+// the sum of per-block counts cost about 4 us each in calls of a few hundred tokens.
 //   vt     [BH][NK][D][64] f16: V^T tile by tile (each key block's transposed values are
 //          one contiguous 16 KB run at d = 128), swap23 key order inside each 16-key
 //          segment; rows past N are zero.
@@ -172,7 +172,8 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
                                                       int N, int NK, int NKr, int NC, int routing,
                                                       const uint16_t* __restrict__ q, float* __restrict__ qbar, int bq,
                                                       int NQ, int NJ, uint32_t* __restrict__ queue,
-                                                      uint32_t* __restrict__ counts, uint32_t count0) {
+                                                      unsigned long long* __restrict__ tally,
+                                                      uint32_t* __restrict__ counts, uint32_t dense) {
     constexpr int CPR = D / 8;          // 16-byte chunks per row
     constexpr int GROUPS = 256 / CPR;   // row groups
     constexpr int VS = D + 2;           // f16 row stride of the staged V tile (odd word count)
@@ -182,7 +183,10 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
     const int cc = t % CPR, g = t / CPR;
 
     if (j == 0) {
-        if (t == 0) counts[bh] = count0;
+        if (t == 0) {
+            if (!routing) counts[bh] = dense;
+            else if (tally) tally[bh] = 0ull;
+        }
         if (bh == 0 && t < 8) queue[32 * t] = 0u;
     }
     if (j >= NJ) {
@@ -959,6 +963,17 @@ __device__ __forceinline__ int route_and_list(const float* __restrict__ qbar_i, 
     return n_sel + (ne - nr);
 }
 
+// Adds a query block's nsel selected pairs to its head's tally: blocks done in the upper half, pairs in the lower (at
+// most NQ * NKr, below 2^32 at every supported length).  The block that completes the head stores the sum, once, so
+// a counts buffer that overlapping calls share always holds one call's whole result.  A head of one block
+// has no tally.  One thread calls it.  The bf16 kernel does so right after the routing (image layer 3,178 ->
+// 3,183 us against an atomic that returns nothing); after the tiles, with nsel held through them, 3,147 -> 3,212.
+__device__ __forceinline__ void tally_block(unsigned long long* tally, uint32_t* counts, int bh, int NQ, int nsel) {
+    unsigned long long old = 0ull;
+    if (NQ > 1) old = atomicAdd(tally + bh, (1ull << 32) | (uint32_t)nsel);
+    if ((uint32_t)(old >> 32) == (uint32_t)NQ - 1u) counts[bh] = (uint32_t)old + (uint32_t)nsel;
+}
+
 // ---------------------------------------------------------------------------
 // Fused routed attention, bf16 inputs.
 // ---------------------------------------------------------------------------
@@ -972,7 +987,8 @@ struct AttnArgs {
     const _Float16* vbarh;
     const float* tau;             // [BH][NQ] thresholds (no causal mask)
     uint16_t* out;
-    uint32_t* counts;             // [BH] selected pairs, added to in the routing modes
+    unsigned long long* tally;    // [BH] see tally_block (routing modes, NQ > 1)
+    uint32_t* counts;             // [BH] selected pairs
     uint32_t* mask_out;
     const uint16_t* order;        // [BH][NQ] query-block order (routing without a causal mask), or null: identity
     uint32_t* queue;              // [8][32] per-XCD claim counters, zero at launch
@@ -1134,7 +1150,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
 
     int nr = a.NKr, ne = a.NK;               // routable blocks [0, nr), forced blocks [nr, ne)
     if constexpr (CAUSAL) causal_ranges<BQ>(qi, a.causal_g, a.N, a.NK, nr, ne);
-    int ntiles, nsel, nuns = 0;
+    int ntiles, nsel = 0, nuns = 0;
     if (MODE == kDense) {
         ntiles = ne;
         nsel = nr;
@@ -1146,7 +1162,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
         if (a.mask_out)
             for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
     }
-    if (MODE != kDense && tid == 0) atomicAdd(a.counts + bh, (uint32_t)nsel);
+    if (MODE != kDense && tid == 0) tally_block(a.tally, a.counts, bh, a.NQ, nsel);
     const int napx = MODE == kSparse ? (nuns + kChunk - 1) / kChunk : 0;   // correction tiles
     // slot of the ragged last key block among the correction slots (it can only be the last one)
     const int last_slot = (nuns > 0 && a.NKr == a.NK && ulist[max(nuns - 1, 0)] == a.NK - 1) ? nuns - 1 : -1;
@@ -1937,6 +1953,7 @@ struct AttnArgsF32 {
     float* out;
     float* part;              // [slot][BQ][D] unnormalised O of the shares past a block's first
     float* part_ml;           // [workgroup][BQ][2] running max (log2 units) and row sum
+    unsigned long long* tally;   // [BH] see tally_block (routing modes, NQ > 1)
     uint32_t* counts;
     uint32_t* mask_out;
     int BH, N, NQ, NK, NKr, NC, MW;
@@ -2020,7 +2037,7 @@ void routed_attn_f32_kernel(AttnArgsF32 a) {
     const int qi = CAUSAL ? a.NQ - 1 - qx : qx;     // causal masks: the longest blocks first
     int nr = a.NKr, ne = a.NK;                      // routable blocks [0, nr), forced blocks [nr, ne)
     if constexpr (CAUSAL) causal_ranges<BQ>(qi, a.causal_g, a.N, a.NK, nr, ne);
-    int ntiles, nsel, nuns = 0;
+    int ntiles, nsel = 0, nuns = 0;
     if (MODE == kDense) {
         ntiles = ne;
         if (tid == 0 && qx == 0 && sp == 0) a.counts[bh] = a.dense_count;
@@ -2033,11 +2050,9 @@ void routed_attn_f32_kernel(AttnArgsF32 a) {
         __builtin_amdgcn_s_setprio(0);
         ntiles = __builtin_amdgcn_readfirstlane(ntiles);   // from LDS, the same in every lane: scalar control flow
         nuns = __builtin_amdgcn_readfirstlane(nuns);
-        if (sp == 0) {
-            if (a.mask_out)
-                for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
-            if (tid == 0) atomicAdd(a.counts + bh, (uint32_t)nsel);
-        }
+        if (sp == 0 && a.mask_out)
+            for (int w = tid; w < a.MW; w += NT) a.mask_out[((size_t)bh * a.NQ + qi) * a.MW + w] = selw[w];
+        nsel = __builtin_amdgcn_readfirstlane(nsel);
     }
     const int napx = MODE == kSparse ? (nuns + kChunk - 1) / kChunk : 0;
     const int T = napx + ntiles;
@@ -2252,6 +2267,7 @@ void routed_attn_f32_kernel(AttnArgsF32 a) {
         else tile(std::integral_constant<int, kEdgeTile>{}, c, nv, n + ns);
     }
 
+    if (MODE != kDense && sp == 0 && tid == 0) tally_block(a.tally, a.counts, bh, a.NQ, nsel);
     float lt = l + __shfl_xor(l, 32);
     if constexpr (KG == 2) {
         // the second key half hands its state to the first through LDS (the stages are free)
@@ -2498,6 +2514,8 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
     } else if (s.mode == kSparse) {
         w.vbar = reinterpret_cast<float*>(take(BH * s.NK * d * 4));
     }
+    // a head of several query blocks only: with one, that block's count is the head's
+    if (routing && s.NQ > 1) w.tally = reinterpret_cast<unsigned long long*>(take(BH * 8));
     if (s.dtype == kBF16) w.queue = reinterpret_cast<uint32_t*>(take(8 * 32 * 4));
     if (s.dtype == kF32) {
         // The workspace query does not know about a mask: the room for partial outputs covers both cases.
@@ -2517,17 +2535,17 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
 }
 
 hipError_t launch_pool(const void* q, const void* k, const void* v, float* qbar, float* kbar, float* vbar,
-                       uint32_t* counts, int dtype, int BH, int N, int d, int bq, int bk, hipStream_t st) {
+                       unsigned long long* tally, int dtype, int BH, int N, int d, int bq, int bk, hipStream_t st) {
     const int nbq = (N + bq - 1) / bq, nbk = (N + bk - 1) / bk;
     const int nq = qbar ? nbq : 0, nk = kbar ? nbk : 0, nv = vbar ? nbk : 0;
     const dim3 grid(nq + nk + nv, BH);
     if (dtype == kBF16)
         pool_kernel<uint16_t><<<grid, dim3(256), 0, st>>>(
             static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), qbar, kbar,
-            vbar, counts, N, d, bq, bk, nbq, nbk, nq, nk);
+            vbar, tally, N, d, bq, bk, nbq, nbk, nq, nk);
     else
         pool_kernel<float><<<grid, dim3(256), 0, st>>>(static_cast<const float*>(q), static_cast<const float*>(k),
-                                                       static_cast<const float*>(v), qbar, kbar, vbar, counts, N, d, bq,
+                                                       static_cast<const float*>(v), qbar, kbar, vbar, tally, N, d, bq,
                                                        bk, nbq, nbk, nq, nk);
     return hipGetLastError();
 }
@@ -2627,15 +2645,15 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         const uint16_t* kk = static_cast<const uint16_t*>(k);
         const uint16_t* vv = static_cast<const uint16_t*>(v);
         const dim3 grid(nj + (routing ? s.NQ : 0), s.BH);
-        const uint32_t count0 = routing ? 0u : dense_count(s);
+        const uint32_t dense = routing ? 0u : dense_count(s);
         if (d == 128)
             prep_kernel<128><<<grid, dim3(256), 0, st>>>(kk, vv, ws.kbar, ws.kbarh, ws.vbarh, ws.vt, s.N, s.NK, s.NKr,
                                                          s.NC, routing ? 1 : 0, qq, ws.qbar, s.bq, s.NQ, nj, ws.queue,
-                                                         counts, count0);
+                                                         ws.tally, counts, dense);
         else
             prep_kernel<64><<<grid, dim3(256), 0, st>>>(kk, vv, ws.kbar, ws.kbarh, ws.vbarh, ws.vt, s.N, s.NK, s.NKr,
                                                         s.NC, routing ? 1 : 0, qq, ws.qbar, s.bq, s.NQ, nj, ws.queue,
-                                                        counts, count0);
+                                                        ws.tally, counts, dense);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (routing) {
             if (!s.causal) {   // causal masks: the kernel takes each row's statistics itself
@@ -2659,6 +2677,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.vbarh = ws.vbarh;
         a.tau = ws.tau;
         a.out = static_cast<uint16_t*>(out);
+        a.tally = ws.tally;
         a.counts = counts;
         a.mask_out = mask_out;
         a.BH = s.BH; a.N = s.N; a.NQ = s.NQ; a.NK = s.NK; a.NKr = s.NKr; a.NC = s.NC; a.MW = s.MW;
@@ -2683,7 +2702,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         if (ev_stop && (e = hipEventRecord(ev_stop, st)) != hipSuccess) return e;
     } else {
         if (routing) {
-            e = launch_pool(q, k, v, ws.qbar, ws.kbar, s.mode == kSparse ? ws.vbar : nullptr, counts, kF32, s.BH, s.N, d,
+            e = launch_pool(q, k, v, ws.qbar, ws.kbar, s.mode == kSparse ? ws.vbar : nullptr, ws.tally, kF32, s.BH, s.N, d,
                             s.bq, s.bk, st);
             if (e != hipSuccess) return e;
             if (!s.causal) {   // causal masks: the kernel takes each row's statistics itself
@@ -2708,6 +2727,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.out = static_cast<float*>(out);
         a.part = ws.part;
         a.part_ml = ws.part_ml;
+        a.tally = ws.tally;
         a.counts = counts;
         a.mask_out = mask_out;
         a.BH = s.BH; a.N = s.N; a.NQ = s.NQ; a.NK = s.NK; a.NKr = s.NKr; a.NC = s.NC; a.MW = s.MW;

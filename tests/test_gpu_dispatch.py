@@ -115,3 +115,43 @@ def test_causal_queue_orders(dev, H, N, d, bq, g, mode):
         if assert_mask_matches(gmask[:, heads], ref["mask"], ref["s_hat"], ref["tau"]):
             ref = ora.forward(qn, kn, vn, bq, 64, 0.5, mode, causal_granule=g, mask=gmask[:, heads])
     assert_output_close(to_np(out)[:, heads], ref["out"], "bf16", mode)
+
+
+@pytest.mark.parametrize("dtype,N,bq", [("bf16", 2048, 128), ("bf16", 1024, 64), ("f32", 1024, 64)])
+def test_counts_shared_by_overlapping_calls_hold_one_calls_sums(dev, dtype, N, bq):
+    # Two forwards with other selections overlap on two streams, each with its own workspace, and write the same
+    # counts buffer (the caller's, then the library's): every head's count is the sum of one of the two calls.
+    w = small_workload("counts", (N,), 128, bq, dtype=dtype, H=24, B=2, seed=13)
+    q, k, v = (t.to(dev) for t in synth.make_qkv(w))
+    code = sb.SOL_BF16 if dtype == "bf16" else sb.SOL_F32
+    ws = [torch.empty(sb.workspace_bytes(w.B, w.H, N, 128, bq, 64, "sparse", code), dtype=torch.uint8, device=dev)
+          for _ in range(2)]
+    outs = [torch.empty_like(q) for _ in range(2)]
+    betas = (0.2, 1.1)
+    want = []
+    for beta, o, s in zip(betas, outs, ws):
+        c = torch.empty((w.B, w.H), dtype=torch.int32, device=dev)
+        sb.forward(q, k, v, bq, 64, beta, "sparse", out=o, workspace=s, counts=c)
+        want.append(c.cpu().numpy().ravel())
+    assert (want[0] != want[1]).all()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]   # default priority
+    shared = torch.empty((w.B, w.H), dtype=torch.int32, device=dev)
+    for counts in (shared, None):
+        for _ in range(5):
+            torch.cuda.synchronize()
+            for i in range(2):
+                with torch.cuda.stream(streams[i]):
+                    sb.forward(q, k, v, bq, 64, betas[i], "sparse", out=outs[i], workspace=ws[i], counts=counts)
+            torch.cuda.synchronize()
+            got = np.array(sb.stats(w.B, w.H, counts=counts)) * (w.NQ * w.NK)
+            assert all(round(g) in (a, b) for g, a, b in zip(got, *want)), (got, want)
+
+
+@pytest.mark.parametrize("dtype,d,bq", [("bf16", 128, 64), ("f32", 64, 128)])
+def test_counts_of_one_query_block(dev, dtype, d, bq):
+    w = small_workload("oneblock", (bq - 3,), d, bq, dtype=dtype, H=3, seed=2)
+    q, k, v = (t.to(dev) for t in synth.make_qkv(w))
+    mask = torch.zeros((1, 3, 1, 1), dtype=torch.int32, device=dev)
+    counts = torch.full((1, 3), -1, dtype=torch.int32, device=dev)
+    sb.forward(q, k, v, bq, 64, 0.0, "sparse", counts=counts, mask_out=mask)
+    assert np.array_equal(counts.cpu().numpy(), sb.unpack_mask(mask.cpu().numpy().view(np.uint32), w.NK).sum(axis=(2, 3)))
