@@ -160,7 +160,12 @@ int sol_attn_forward(const void* q, const void* k, const void* v, void* out,
  *   in the routing statistics or the counts.  0 for none.
  * workspace/workspace_bytes: caller device scratch of at least
  *   sol_attn_workspace_bytes(...) bytes, or NULL/0 to let the library allocate
- *   (and keep, growing on demand) its own.  It holds the pre-pass results and
+ *   (and keep, growing on demand) its own.  With f32 inputs a part of those bytes
+ *   is room for partial outputs, which short launches use to share query blocks
+ *   between workgroups; that part does not grow with N throughout.  A workspace
+ *   that lacks only this room is taken too: blocks are then computed whole
+ *   (slower, results within rounding), so a workspace sized for the longest
+ *   sequence serves every shorter one.  It holds the pre-pass results and
  *   the fused kernel's work-queue counters, so two calls that may run at the
  *   same time (different streams) need different workspaces; calls that pass
  *   NULL share the library's one per device.
@@ -242,8 +247,8 @@ int sol_attn_forward_noalloc(const void* q, const void* k, const void* v, void* 
                              float tau, int mode, int dtype, int keep_tail_tokens,
                              uint32_t* counts, uint32_t* mask_out, void* stream);
 
-/* Device workspace bytes sol_attn_forward_ex needs for these arguments, or 0
- * if they are invalid/unsupported. */
+/* Device workspace bytes sol_attn_forward_ex uses for these arguments (f32: with
+ * the room for partial outputs), or 0 if they are invalid/unsupported. */
 size_t sol_attn_workspace_bytes(int B, int H, int N, int d, int block_q, int block_k,
                                 int mode, int dtype, int keep_tail_tokens);
 

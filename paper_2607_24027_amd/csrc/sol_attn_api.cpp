@@ -292,9 +292,9 @@ int forward_impl(const void* q, const void* k, const void* v, void* out, int B, 
                               causal_granule);
     if (rc) return rc;
     const sol::Shape s = sol::make_shape(B, H, N, d, block_q, block_k, mode, dtype, keep_tail_tokens, causal_granule);
-    const size_t need = sol::workspace_layout(s, nullptr, nullptr);
-    if (workspace && workspace_bytes < need)
-        return fail(SOL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu bytes required", workspace_bytes, need);
+    const size_t least = sol::workspace_layout(s, nullptr, nullptr, 0);
+    if (workspace && workspace_bytes < least)
+        return fail(SOL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu bytes required", workspace_bytes, least);
     hipStream_t st = static_cast<hipStream_t>(stream);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -303,6 +303,7 @@ int forward_impl(const void* q, const void* k, const void* v, void* out, int B, 
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceBuffers& db = g_bufs[dev];
     if (!workspace) {
+        const size_t need = sol::workspace_layout(s, nullptr, nullptr);
         if (db.ws_bytes < need) {
             if (db.ws) {
                 e = hipDeviceSynchronize();
@@ -316,6 +317,7 @@ int forward_impl(const void* q, const void* k, const void* v, void* out, int B, 
             db.ws_bytes = need;
         }
         workspace = db.ws;
+        workspace_bytes = db.ws_bytes;
     }
     if (!counts) {
         const size_t n = (size_t)s.BH;
@@ -335,7 +337,7 @@ int forward_impl(const void* q, const void* k, const void* v, void* out, int B, 
         counts = db.counts;
     }
     sol::Workspace ws;
-    sol::workspace_layout(s, static_cast<char*>(workspace), &ws);
+    sol::workspace_layout(s, static_cast<char*>(workspace), &ws, workspace_bytes);
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (g_timing.enabled && g_timing.device == dev && g_timing.used < kMaxTimed) {
         ev0 = g_timing.start[g_timing.used];
@@ -381,7 +383,7 @@ int sol_attn_forward_noalloc(const void* q, const void* k, const void* v, void* 
     if (rc) return rc;
     if (!counts) return fail(SOL_ERR_INVALID_ARG, "counts must be given: this entry point allocates nothing");
     const sol::Shape s = sol::make_shape(B, H, N, d, block_q, block_k, mode, dtype, keep_tail_tokens);
-    const size_t need = sol::workspace_layout(s, nullptr, nullptr);
+    const size_t need = sol::workspace_layout(s, nullptr, nullptr, 0);
     const size_t have = sol::noalloc_scratch_bytes();
     if (need > have)
         return fail(SOL_ERR_WORKSPACE,

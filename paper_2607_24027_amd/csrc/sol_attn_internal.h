@@ -69,8 +69,9 @@ struct Workspace {
     F32Units units;
 };
 
-// Returns the byte size; fills *ws when base != nullptr.
-size_t workspace_layout(const Shape& s, char* base, Workspace* ws);
+// Returns the byte size; fills *ws when base != nullptr.  have: the workspace's bytes.  The room for partial outputs
+// (f32) is taken only where `have` holds it; have = 0 gives the bytes without it, which every call needs.
+size_t workspace_layout(const Shape& s, char* base, Workspace* ws, size_t have = SIZE_MAX);
 
 // Dynamic LDS bytes of the fused attention kernel for this shape.
 size_t attn_lds_bytes(const Shape& s);

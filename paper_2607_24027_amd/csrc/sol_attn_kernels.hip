@@ -2485,7 +2485,7 @@ F32Units f32_units(const Shape& s, size_t base_bytes) {
     return t;
 }
 
-size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
+size_t workspace_layout(const Shape& s, char* base, Workspace* ws, size_t have) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> char* {
         char* p = base ? base + off : nullptr;
@@ -2524,7 +2524,9 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws) {
         const int blocks = s.BH * s.NQ;
         w.units = f32_units(s, off);
         const size_t room = std::max(w.units.bytes(blocks, s.bq, s.d), f32_units(other, off).bytes(blocks, s.bq, s.d));
-        if (room > 0) {
+        if (off + room > have) {   // a workspace without that room: whole blocks
+            w.units = F32Units{(blocks + 7) / 8 * 8, 1, 1};
+        } else if (room > 0) {
             char* p = take(room);
             w.part = reinterpret_cast<float*>(p);
             w.part_ml = reinterpret_cast<float*>(p + w.units.slots(blocks) * s.bq * d * 4);

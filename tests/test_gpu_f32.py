@@ -101,3 +101,23 @@ def test_f32_tensors_off_16_bytes(dev, mode, g, d, bq):
     ref = sb.forward(*aligned, bq, 64, 0.5, mode, causal_granule=g)
     sb.forward(*off, bq, 64, 0.5, mode, causal_granule=g, out=out)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("mode", ["dense", "sparse"])
+def test_f32_workspace_of_a_longer_sequence_serves_a_shorter_one(dev, mode):
+    # 512 query blocks want less room for partial outputs than 504: the longer call's workspace holds all that the
+    # shorter one needs but that room, and its blocks are computed whole
+    H, d, bq = 8, 128, 64
+    size = {n: sb.workspace_bytes(1, H, n, d, bq, 64, mode, sb.SOL_F32) for n in (4032, 4096)}
+    assert size[4032] > size[4096]
+    w = small_workload("f32ws", (4032,), d, bq, dtype="f32", H=H, seed=6)
+    q, k, v = (t.to(dev) for t in synth.make_qkv(w))
+    ref = sb.forward(q, k, v, bq, 64, 0.5, mode)
+    guard = 1 << 16
+    buf = torch.full((size[4096] + guard,), 0x5A, dtype=torch.uint8, device=dev)
+    out = sb.forward(q, k, v, bq, 64, 0.5, mode, workspace=buf[:size[4096]])
+    assert bool((buf[size[4096]:] == 0x5A).all()), "written past the workspace"
+    assert_output_close(to_np(out), to_np(ref), "f32", mode)
+    with pytest.raises(sb.SolAttnError) as ei:
+        sb.forward(q, k, v, bq, 64, 0.5, "sparse", workspace=buf[:1 << 20])
+    assert ei.value.code == sb.SOL_ERR_WORKSPACE
