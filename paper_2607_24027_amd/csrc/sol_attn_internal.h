@@ -44,9 +44,6 @@ struct F32Units {
         return slots(blocks) ? slots(blocks) * bq * d * 4 + (size_t)units(blocks) * bq * 8 : 0;
     }
 };
-// The whole workspace stays within kSplitRoom when partial outputs are part of it: that is the size of the
-// built-in scratch of the entry point that allocates nothing, so every entry point shares alike.
-constexpr size_t kSplitRoom = (size_t)64 << 20;
 
 // Workspace carve-up (all device pointers, 256-byte aligned inside one buffer).
 struct Workspace {

@@ -2465,8 +2465,10 @@ size_t attn_lds_bytes(const Shape& s) {
 //   fewer than 512          two shares for the first three quarters, six for the rest: the small shares fill
 //                           the CUs whose blocks were short
 //   more                    whole blocks, and four shares for the last 128, which even out the end
-// No more shares than leave four key blocks each, and partial outputs only within kSplitRoom.
-F32Units f32_units(const Shape& s, size_t base_bytes) {
+// No more shares than leave four key blocks each.  The partial outputs take at most about 70 MB (1,051 slots of
+// 64 KB at 511 blocks).  Neither the mode nor the routing's buffers enter: dense and sparse calls of a shape share
+// alike, so that with every block selected they accumulate in the same order.
+F32Units f32_units(const Shape& s) {
     const int blocks = s.BH * s.NQ, all = (blocks + 7) / 8 * 8;
     const int most = std::max(1, std::min(8, s.NK / 4));
     F32Units t;
@@ -2481,11 +2483,11 @@ F32Units f32_units(const Shape& s, size_t base_bytes) {
         t.nb1 = (blocks - 128) / 8 * 8;
         t.ns2 = std::min(most, 4);
     }
-    if (base_bytes + t.bytes(blocks, s.bq, s.d) > kSplitRoom) t = F32Units{all, 1, 1};
     return t;
 }
 
-size_t workspace_layout(const Shape& s, char* base, Workspace* ws, size_t have) {
+// The buffers every call of the shape needs, from `base` on; returns their bytes.
+size_t base_layout(const Shape& s, char* base, Workspace& w) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> char* {
         char* p = base ? base + off : nullptr;
@@ -2494,7 +2496,6 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws, size_t have) 
     };
     const size_t BH = s.BH, d = s.d;
     const bool routing = s.mode != kDense;
-    Workspace w;
     if (routing) {
         w.qbar = reinterpret_cast<float*>(take(BH * s.NQ * d * 4));
         w.kbar = reinterpret_cast<float*>(take(BH * s.NK * d * 4));
@@ -2517,23 +2518,34 @@ size_t workspace_layout(const Shape& s, char* base, Workspace* ws, size_t have) 
     // a head of several query blocks only: with one, that block's count is the head's
     if (routing && s.NQ > 1) w.tally = reinterpret_cast<unsigned long long*>(take(BH * 8));
     if (s.dtype == kBF16) w.queue = reinterpret_cast<uint32_t*>(take(8 * 32 * 4));
+    return off;
+}
+
+size_t workspace_layout(const Shape& s, char* base, Workspace* ws, size_t have) {
+    Workspace w;
+    size_t bytes = base_layout(s, base, w);
     if (s.dtype == kF32) {
-        // The workspace query does not know about a mask: the room for partial outputs covers both cases.
-        Shape other = s;
+        // Partial outputs start where the largest mode's buffers end and cover the call with and without a causal
+        // mask (the workspace query does not know about one): whether a workspace holds them, and with that the
+        // sharing, then depends on the shape and the workspace alone.
+        Shape largest = s, other = s;
+        largest.mode = kSparse;
         other.causal = s.causal ? 0 : 1;
+        Workspace unused;
+        const size_t at = base_layout(largest, nullptr, unused);
         const int blocks = s.BH * s.NQ;
-        w.units = f32_units(s, off);
-        const size_t room = std::max(w.units.bytes(blocks, s.bq, s.d), f32_units(other, off).bytes(blocks, s.bq, s.d));
-        if (off + room > have) {   // a workspace without that room: whole blocks
-            w.units = F32Units{(blocks + 7) / 8 * 8, 1, 1};
-        } else if (room > 0) {
-            char* p = take(room);
-            w.part = reinterpret_cast<float*>(p);
-            w.part_ml = reinterpret_cast<float*>(p + w.units.slots(blocks) * s.bq * d * 4);
+        w.units = f32_units(s);
+        const size_t room = std::max(w.units.bytes(blocks, s.bq, s.d), f32_units(other).bytes(blocks, s.bq, s.d));
+        if (room == 0 || at + room > have) {
+            w.units = F32Units{(blocks + 7) / 8 * 8, 1, 1};   // whole blocks
+        } else {
+            bytes = at + room;
+            w.part = base ? reinterpret_cast<float*>(base + at) : nullptr;
+            w.part_ml = base ? reinterpret_cast<float*>(base + at + w.units.slots(blocks) * s.bq * s.d * 4) : nullptr;
         }
     }
     if (ws) *ws = w;
-    return off;
+    return bytes;
 }
 
 hipError_t launch_pool(const void* q, const void* k, const void* v, float* qbar, float* kbar, float* vbar,

@@ -121,3 +121,24 @@ def test_f32_workspace_of_a_longer_sequence_serves_a_shorter_one(dev, mode):
     with pytest.raises(sb.SolAttnError) as ei:
         sb.forward(q, k, v, bq, 64, 0.5, "sparse", workspace=buf[:1 << 20])
     assert ei.value.code == sb.SOL_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("H,N,d,bq,text", [(8, 7680, 128, 128, 0), (17, 1985, 64, 64, 64), (2, 1087, 64, 128, 0)])
+def test_f32_every_block_selected_is_dense_bit_for_bit(dev, H, N, d, bq, text):
+    # the sharing of query blocks must not depend on the mode, whichever workspace the calls have: 480 blocks whose
+    # partial outputs and routing buffers exceed 64 MiB together, launches of more and of fewer blocks
+    w = small_workload("f32dense", (N - text,), d, bq, dtype="f32", text_tokens=text, H=H, seed=8)
+    q, k, v = (t.to(dev) for t in synth.make_qkv(w))
+    dense = sb.forward(q, k, v, bq, 64, 0.0, "dense")
+    assert torch.equal(sb.forward(q, k, v, bq, 64, -math.inf, "sparse", keep_tail_tokens=text), dense)
+    outs = [torch.empty_like(q) for _ in range(2)]
+    counts = torch.empty((1, H), dtype=torch.int32, device=dev)
+    sb.forward_noalloc(q, k, v, outs[0], counts, bq, 64, 0.0, "dense")
+    sb.forward_noalloc(q, k, v, outs[1], counts, bq, 64, -math.inf, "sparse")
+    assert torch.equal(outs[0], outs[1])
+    size = [sb.workspace_bytes(1, H, N, d, bq, 64, m, sb.SOL_F32) for m in ("dense", "sparse")]
+    assert size[0] == size[1]   # one room for partial outputs
+    ws = torch.empty(size[0] - 256, dtype=torch.uint8, device=dev)   # just short of it
+    for o, (beta, m) in zip(outs, ((0.0, "dense"), (-math.inf, "sparse"))):
+        sb.forward(q, k, v, bq, 64, beta, m, out=o, workspace=ws)
+    assert torch.equal(outs[0], outs[1])
