@@ -2337,7 +2337,7 @@ __global__ __launch_bounds__(256) void finish_kernel(const float* __restrict__ p
         const float w = ms == kNegInf ? 0.f : __builtin_amdgcn_exp2f(ms - mm);
         l = fmaf(w, ml[2 * s * BQ + 1], l);
         const f32x4 x = *reinterpret_cast<const f32x4*>(s == 0 ? o : part + (size_t)(s - 1) * BQ * D);
-        if (w > 0.f) acc += w * x;
+        acc += w * x;   // no share is skipped by its weight: 0 times a share that is not finite is not a number
     }
     *reinterpret_cast<f32x4*>(o) = acc * (l > 0.f ? 1.0f / l : 0.f);
 }

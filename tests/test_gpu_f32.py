@@ -142,3 +142,21 @@ def test_f32_every_block_selected_is_dense_bit_for_bit(dev, H, N, d, bq, text):
     for o, (beta, m) in zip(outs, ((0.0, "dense"), (-math.inf, "sparse"))):
         sb.forward(q, k, v, bq, 64, beta, m, out=o, workspace=ws)
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("H,N,d,bq", [(2, 1024, 128, 64), (2, 1087, 64, 128), (20, 1984, 64, 64)])
+def test_f32_infinite_scores_reach_the_output(dev, H, N, d, bq):
+    # One key component is infinite.  Rows that score it +inf have no finite softmax and must not come out finite,
+    # whichever share of the block held the key; rows that score it -inf give it no weight, as for a huge finite
+    # component of the same sign.
+    w = small_workload("f32score", (N,), d, bq, dtype="f32", H=H, seed=12)
+    q, k, v = synth.make_qkv(w)
+    low = q[..., 0] < 0
+    for key in (5, N // 2, N - 1):
+        res = []
+        for x in (math.inf, 1e30):
+            kk = k.clone()
+            kk[:, :, key, 0] = x
+            res.append(sb.forward(q.to(dev), kk.to(dev), v.to(dev), bq, 64, 0.0, "dense").cpu())
+        assert not torch.isfinite(res[0][~low]).any()
+        assert torch.equal(res[0][low], res[1][low])
