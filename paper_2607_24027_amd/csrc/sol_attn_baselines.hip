@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sha
     int seen = 0;
 #pragma unroll
     for (int i = 0; i < KPL; ++i) {
-        const bool is_eq = key[i] == kth && key[i] != 0u;
+        const bool is_eq = key[i] == kth && (int)(threadIdx.x & 63) + 64 * i < NKr;   // kth may be 0
         const uint64_t eq = __ballot(is_eq);
         store_words(words, MW, i, __ballot(key[i] > kth || (is_eq && seen + bits_below(eq) < take_eq)));
         seen += __popcll(eq);
@@ -178,23 +178,24 @@ __global__ __launch_bounds__(256) void topp_kernel(const float* __restrict__ sha
         for (int i = 0; i < KPL; ++i) m += key[i] > c ? w[i] : 0.f;
         return wave_sum(m);
     };
-    // c: the smallest value whose mass above is below the limit; below it (c - 1) the mass reaches the limit
-    uint32_t c = 0u;
-    float above = mass_above(0u);
-    if (!(above < limit)) {
-        uint32_t low = 0u;   // the mass above `low` reaches the limit
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t cand = low | (1u << bit);
-            if (!(mass_above(cand) < limit)) low = cand;
-        }
-        c = low + 1u;
-        above = mass_above(c);
-    }
     uint32_t* words = mask + r * MW;
+    // A row with a proxy of +inf or not a number, or with -inf throughout, has no softmax: no block is kept.  The test
+    // is on the limit's bits (positive and finite otherwise), since comparisons assume numbers here.
+    if (__float_as_uint(limit) - 1u >= 0x7F7FFFFFu) {
+        for (int w0 = lane; w0 < MW; w0 += 64) words[w0] = 0u;
+        return;
+    }
+    uint32_t low = 0u;   // the mass above `low` reaches the limit (above 0 it is the total, and p <= 1)
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t cand = low | (1u << bit);
+        if (!(mass_above(cand) < limit)) low = cand;
+    }
+    const uint32_t c = low + 1u;   // the smallest value whose mass above is below the limit
+    const float above = mass_above(c);
     int seen = 0;
 #pragma unroll
     for (int i = 0; i < KPL; ++i) {
-        const bool is_eq = key[i] == c && key[i] != 0u;
+        const bool is_eq = key[i] == c;
         const uint64_t eq = __ballot(is_eq);
         store_words(words, MW, i,
                     __ballot(key[i] > c || (is_eq && above + (float)(seen + bits_below(eq)) * w[i] < limit)));

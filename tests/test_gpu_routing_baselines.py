@@ -58,3 +58,26 @@ def test_topk_longest_row(dev):
     prox, mask = sb.route_materialized(q, k, "topk", 1000)
     got = sb.unpack_mask(mask.cpu().numpy().view(np.uint32), 8192)
     assert np.array_equal(got, ora.route_topk(prox.cpu().numpy().astype(np.float64), 1000))
+
+
+@pytest.mark.parametrize("nkr,d", [(100, 64), (300, 128)])
+def test_rows_without_a_softmax(dev, nkr, d):
+    # One key component is infinite: rows whose query component is positive have a proxy of +inf, zero gives not a
+    # number, and both have no softmax, so top-p keeps nothing; a negative one gives -inf, a block without weight.
+    q, k = pooled(9, nkr, d, False, dev)
+    q[..., 0] = torch.tensor([1.0, 0.0, -1.0], device=dev).repeat(3)
+    k[:, 1, nkr // 2, 0] = float("inf")   # the second head; the first stays finite
+    prox, mask = sb.route_materialized(q, k, "topp", 0.5)
+    s = prox.cpu().numpy().astype(np.float64)
+    got = sb.unpack_mask(mask.cpu().numpy().view(np.uint32), nkr)
+    for h in range(2):
+        for i in range(9):
+            if h == 1 and i % 3 < 2:
+                assert not got[0, h, i].any()
+                continue
+            assert not got[0, h, i][np.isneginf(s[0, h, i])].any()
+            w = np.exp(s[0, h, i] - s[0, h, i].max())
+            mass = w[got[0, h, i]].sum() / w.sum()
+            assert 0.5 - 1e-5 <= mass <= 0.5 + w[got[0, h, i]].min() / w.sum() + 1e-5
+    _, mask = sb.route_materialized(q, k, "topk", 7)
+    assert (sb.unpack_mask(mask.cpu().numpy().view(np.uint32), nkr).sum(-1) == 7).all()
