@@ -9,6 +9,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "sol_attn_internal.h"
@@ -47,16 +48,50 @@ struct DeviceBuffers {
 std::mutex g_mu;
 std::map<int, DeviceBuffers> g_bufs;
 
-// Moment scratch of sol_attn_thresholds, one buffer per device, grown on demand up to kMaxMomentBytes and given back by
-// sol_attn_release; larger ones live for one call.  The mutex is held from the launches to the end of the
-// call's synchronisation, so no two calls share the buffer.
+// Moment scratch of sol_attn_thresholds.  Each device keeps one idle buffer of at most kMaxMomentBytes.  A call takes
+// it out of the map for its own use (or allocates, when it is taken or too small), and puts its buffer back once
+// its stream has been waited for: no call waits for another's stream, and a buffer in the map is never in use.
+// sol_attn_release frees the idle buffers and advances g_mom_epoch, so that a call in flight across it frees its
+// own instead of putting it back.
 std::mutex g_mom_mu;
 struct MomentBuffer {
     void* p = nullptr;
     size_t bytes = 0;
 };
 std::map<int, MomentBuffer> g_mom;
+unsigned g_mom_epoch = 0;
 constexpr size_t kMaxMomentBytes = (size_t)96 << 20;
+
+// A buffer of at least `need` bytes on the current device `dev`.
+hipError_t take_moment_buffer(int dev, size_t need, MomentBuffer* buf, unsigned* epoch) {
+    MomentBuffer idle;
+    {
+        std::lock_guard<std::mutex> lock(g_mom_mu);
+        *epoch = g_mom_epoch;
+        MomentBuffer& slot = g_mom[dev];
+        if (slot.bytes >= need || need <= kMaxMomentBytes) {   // one that is kept afterwards replaces the idle one
+            idle = slot;
+            slot = MomentBuffer{};
+        }
+    }
+    if (idle.bytes >= need) {
+        *buf = idle;
+        return hipSuccess;
+    }
+    if (idle.p) (void)hipFree(idle.p);
+    buf->bytes = need;
+    return hipMalloc(&buf->p, need);
+}
+
+// Puts a buffer that no kernel uses any more back, or frees it.
+void return_moment_buffer(int dev, MomentBuffer buf, unsigned epoch) {
+    if (buf.bytes <= kMaxMomentBytes) {
+        std::lock_guard<std::mutex> lock(g_mom_mu);
+        MomentBuffer& slot = g_mom[dev];
+        if (epoch == g_mom_epoch && slot.bytes < buf.bytes) std::swap(slot, buf);
+    }
+    if (buf.p) (void)hipFree(buf.p);
+}
 
 // What sol_attn_stats needs to turn a counts buffer into fractions: one record per counts
 // buffer a forward wrote (keyed by its device address), with an event recorded on the
@@ -166,25 +201,22 @@ int sol_attn_thresholds(const float* qbar, const float* kbar, float* tau, float*
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-    std::lock_guard<std::mutex> lock(g_mom_mu);
-    MomentBuffer& buf = g_mom[dev];
-    void* mom = buf.p;
-    if (buf.bytes < need) {
-        e = hipMalloc(&mom, need);
-        if (e != hipSuccess) return hip_fail(e, "hipMalloc(moments)");
-        if (need <= kMaxMomentBytes) {
-            if (buf.p) (void)hipFree(buf.p);   // idle: every call waits for its kernels
-            buf = MomentBuffer{mom, need};
-        }
-    }
-    double* scratch = static_cast<double*>(mom);
-    float* cov = reinterpret_cast<float*>(static_cast<char*>(mom) + part);
+    MomentBuffer buf;
+    unsigned epoch = 0;
+    e = take_moment_buffer(dev, need, &buf, &epoch);
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc(moments)");
+    double* scratch = static_cast<double*>(buf.p);
+    float* cov = reinterpret_cast<float*>(static_cast<char*>(buf.p) + part);
     float* muk = cov + (size_t)BH * d * d;
     e = sol::launch_moments(kbar, muk, cov, scratch, BH, NK, nk_routable, d, st);
     if (e == hipSuccess) e = sol::launch_tau(qbar, muk, cov, tau, mu, sigma, BH, NQ, d, beta,
                                                     threshold_mode == SOL_THRESHOLD_DIAGONAL ? 1 : 0, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (mom != buf.p) (void)hipFree(mom);
+    // The stream is waited for after a failed launch too: an earlier one may be running.  A buffer whose kernels could
+    // not be waited for is not used again (hipFree waits for the device).
+    const hipError_t waited = hipStreamSynchronize(st);
+    if (waited == hipSuccess) return_moment_buffer(dev, buf, epoch);
+    else (void)hipFree(buf.p);
+    if (e == hipSuccess) e = waited;
     if (e != hipSuccess) return hip_fail(e, "threshold kernels");
     return ok();
 }
@@ -488,6 +520,7 @@ int sol_attn_release(void) {
         if (kv.second.p) (void)hipFree(kv.second.p);
     }
     g_mom.clear();
+    ++g_mom_epoch;
     for (auto& kv : g_bufs) {
         (void)hipSetDevice(kv.first);
         (void)hipDeviceSynchronize();
