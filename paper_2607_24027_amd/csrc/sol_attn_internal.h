@@ -70,7 +70,7 @@ struct Workspace {
 // (f32) is taken only where `have` holds it; have = 0 gives the bytes without it, which every call needs.
 size_t workspace_layout(const Shape& s, char* base, Workspace* ws, size_t have = SIZE_MAX);
 
-// Dynamic LDS bytes of the fused attention kernel for this shape.
+// LDS bytes that bound the accepted lengths: what the fused attention kernel takes (bf16), or more (f32).
 size_t attn_lds_bytes(const Shape& s);
 
 // Block means of q (blocks of bq), k and v (blocks of bk); an output may be null.  tally (or null) is cleared.

@@ -2348,6 +2348,10 @@ hipError_t allow_lds(K kernel, size_t bytes) {
                                (int)bytes);
 }
 
+// Proxies of a row that the f32 kernel keeps in LDS, and its LDS bytes.
+int f32_prox_n(const Shape& s) { return s.causal && s.mode != kDense ? s.NKr : 0; }
+size_t f32_lds_bytes(const Shape& s) { return LdsF32(s.d, s.MW, s.NC, s.NK, f32_prox_n(s)).bytes; }
+
 template <int D, int BQ, int MODE, bool CAUSAL>
 hipError_t launch_attn_bf16(const Shape& s, const AttnArgs& a, hipStream_t st) {
     size_t lds = attn_lds_bytes(s);
@@ -2375,7 +2379,7 @@ hipError_t launch_attn_bf16(const Shape& s, const AttnArgs& a, hipStream_t st) {
 
 template <int D, int BQ, int MODE, bool CAUSAL>
 hipError_t launch_attn_f32(const Shape& s, const AttnArgsF32& a, hipStream_t st) {
-    const size_t lds = LdsF32(D, a.MW, a.NC, a.NK, a.prox_n).bytes;
+    const size_t lds = f32_lds_bytes(s);
     auto kern = routed_attn_f32_kernel<D, BQ, MODE, CAUSAL>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
@@ -2442,17 +2446,18 @@ Shape make_shape(int B, int H, int N, int d, int bq, int bk, int mode, int dtype
 }
 
 size_t attn_lds_bytes(const Shape& s) {
+    if (s.dtype == kF32) {
+        // What the f32 kernel takes, and d * bq floats more, which bound the lengths the f32 path accepts (7,680 key
+        // blocks at d = 128 with 128-row blocks, 3,960 causal): the bytes of a launch never exceed those checked.
+        return f32_lds_bytes(s) + (size_t)s.d * s.bq * 4;
+    }
     // scan scratch, selection words, lists, then (16-byte aligned) the words' prefix counts
     size_t rest = 64 + 4 * (size_t)((s.MW + 3) & ~3) + 2 * ((size_t)s.NC * kChunk + s.NK);
     rest = ((rest + 15) & ~(size_t)15) + 4 * (size_t)((s.MW + 3) & ~3);
-    if (s.dtype == kBF16) {
-        const size_t stage = (size_t)kBlockK * s.d * 2 * 2;
-        // proxies of a causal row: in the tile stages when they fit (the kernel decides alike)
-        if (s.causal && s.mode != kDense && 4 * (size_t)s.NKr > 2 * stage) rest += 4 * (size_t)s.NKr;
-        return 2 * stage + rest;
-    }
-    if (s.causal && s.mode != kDense) rest += 4 * (size_t)s.NKr;   // proxies of a row
-    return (size_t)2 * kBlockK * s.d * 4 + (size_t)s.d * s.bq * 4 + rest;
+    const size_t stage = (size_t)kBlockK * s.d * 2 * 2;
+    // proxies of a causal row: in the tile stages when they fit (the kernel decides alike)
+    if (s.causal && s.mode != kDense && 4 * (size_t)s.NKr > 2 * stage) rest += 4 * (size_t)s.NKr;
+    return 2 * stage + rest;
 }
 
 // How many workgroups share a query block of the f32 kernel.  The chip holds 512 of them, two a CU; a block
@@ -2735,7 +2740,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.kbar = ws.kbar;
         a.vbar = ws.vbar;
         a.tau = ws.tau;
-        a.prox_n = routing && s.causal ? s.NKr : 0;
+        a.prox_n = f32_prox_n(s);
         a.aligned = ((reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v) |
                       reinterpret_cast<uintptr_t>(ws.kbar) | reinterpret_cast<uintptr_t>(ws.vbar)) & 15) == 0;
         a.out = static_cast<float*>(out);

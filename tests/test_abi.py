@@ -105,6 +105,19 @@ def test_causal_sizes_accepted_without_mask():
     assert sb.workspace_bytes(1, 2, 64 * 16385, 128, 128, 64, "sparse") > 0
 
 
+@pytest.mark.parametrize("d,bq,blocks,causal_blocks", [(64, 64, 26944, 13888), (64, 128, 23104, 11904),
+                                                       (128, 64, 15376, 7936), (128, 128, 7680, 3960)])
+def test_longest_f32_sequences(d, bq, blocks, causal_blocks):
+    # key blocks of the longest accepted f32 sequence; one more is refused, also where the kernel's LDS would hold it
+    f32 = sb.SOL_F32
+    assert sb.workspace_bytes(1, 1, 64 * blocks, d, bq, 64, "sparse", f32) > 0
+    assert sb.workspace_bytes(1, 1, 64 * blocks + 1, d, bq, 64, "sparse", f32) == 0
+    tiny = (P(0x6000), 16, None, None, None)   # a workspace too small for any shape: refused right after validation
+    call = sb.lib().sol_attn_forward_causal
+    assert call(*FAKE, 1, 1, 64 * causal_blocks, d, bq, 64, 0.5, 1, f32, 1, *tiny) == sb.SOL_ERR_WORKSPACE
+    assert call(*FAKE, 1, 1, 64 * causal_blocks + 1, d, bq, 64, 0.5, 1, f32, 1, *tiny) == sb.SOL_ERR_UNSUPPORTED
+
+
 def test_other_entry_points_validate():
     lib = sb.lib()
     assert lib.sol_attn_forward(None, None, None, None, 1, 1, 64, 64, 64, 64, 0.0, 1) == sb.SOL_ERR_INVALID_ARG
