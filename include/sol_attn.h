@@ -4,7 +4,8 @@
  * proxy-score reuse fused into one online-softmax pass).
  *
  * All tensors are caller-owned, contiguous, row-major device buffers of shape
- * [B, H, N, d] (row stride d) unless stated otherwise.  Every entry point
+ * [B, H, N, d] (row stride d) unless stated otherwise, aligned to their element
+ * type (k, and in f32 v, are read faster when they start on 16 bytes).  Every entry point
  * validates its arguments on the host and returns a negative error code before
  * any GPU call when they are invalid; sol_attn_last_error() then describes the
  * problem.  Compute calls are asynchronous on the given HIP stream (a
@@ -234,10 +235,10 @@ int sol_attn_forward_causal(const void* q, const void* k, const void* v, void* o
  * Arguments as sol_attn_forward_ex without the workspace; counts is required
  * (the library's own counts buffer would have to be allocated).  The scratch
  * is a 64 MiB array per GPU, held from the library's load until the process
- * ends; a shape whose sol_attn_workspace_bytes() exceeds it returns
- * SOL_ERR_WORKSPACE before any GPU call.  Every call on one GPU uses that
+ * ends; a shape that needs more (f32: without the room for partial outputs)
+ * returns SOL_ERR_WORKSPACE before any GPU call.  Every call on one GPU uses that
  * GPU's one array (everything it needs zeroed is cleared on the call's stream
- * by a fill kernel), so two calls that overlap on one GPU (different streams
+ * by the call's own kernels), so two calls that overlap on one GPU (different streams
  * or threads) race and give undefined results: serialise them.  The counts it
  * writes are not tracked for sol_attn_stats (tracking creates an event):
  * frac[b*H+h] = counts[b*H+h] / (NQ * NKr).
@@ -248,7 +249,7 @@ int sol_attn_forward_noalloc(const void* q, const void* k, const void* v, void* 
                              uint32_t* counts, uint32_t* mask_out, void* stream);
 
 /* Device workspace bytes sol_attn_forward_ex uses for these arguments (f32: with
- * the room for partial outputs), or 0 if they are invalid/unsupported. */
+ * the room for partial outputs), wherever the workspace starts, or 0 if they are invalid/unsupported. */
 size_t sol_attn_workspace_bytes(int B, int H, int N, int d, int block_q, int block_k,
                                 int mode, int dtype, int keep_tail_tokens);
 

@@ -253,7 +253,7 @@ size_t sol_attn_workspace_bytes(int B, int H, int N, int d, int block_q, int blo
                          keep_tail_tokens) != SOL_OK)
         return 0;
     const sol::Shape s = sol::make_shape(B, H, N, d, block_q, block_k, mode, dtype, keep_tail_tokens);
-    return sol::workspace_layout(s, nullptr, nullptr);
+    return sol::workspace_layout(s, nullptr, nullptr) + 16;   // for a workspace that does not start on 16 bytes
 }
 
 }  // extern "C"
@@ -325,8 +325,15 @@ int forward_impl(const void* q, const void* k, const void* v, void* out, int B, 
     if (rc) return rc;
     const sol::Shape s = sol::make_shape(B, H, N, d, block_q, block_k, mode, dtype, keep_tail_tokens, causal_granule);
     const size_t least = sol::workspace_layout(s, nullptr, nullptr, 0);
-    if (workspace && workspace_bytes < least)
-        return fail(SOL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu bytes required", workspace_bytes, least);
+    // Direct copies to LDS and 64-bit atomics: the workspace is used from its first multiple of 16 bytes on.
+    const size_t skip = (size_t)(-reinterpret_cast<uintptr_t>(workspace) & 15);
+    if (workspace && (workspace_bytes < skip || workspace_bytes - skip < least))
+        return fail(SOL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu bytes required", workspace_bytes,
+                    least + skip);
+    if (workspace) {
+        workspace = static_cast<char*>(workspace) + skip;
+        workspace_bytes -= skip;
+    }
     hipStream_t st = static_cast<hipStream_t>(stream);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);

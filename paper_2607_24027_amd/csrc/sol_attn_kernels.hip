@@ -995,6 +995,8 @@ struct AttnArgs {
     int resident;                 // workgroups per XCD in the persistent grid (grid / 8)
     int hlog;                     // log2 of the heads whose blocks are in the queues at once (no causal mask)
     int BH, N, NQ, NK, NKr, NC, MW, per_x;
+    int kfull;                    // key blocks [0, kfull) are whole and start on 16 bytes: N / 64, or 0
+    int kaligned;                 // k starts on 16 bytes (direct copies to LDS)
     float scale, c_log2;
     float bias_full, bias_last;   // log2(n_j)/c_log2 for full blocks and for the last block
     int causal_g;                 // causal granule G (CAUSAL kernels): key s visible to query t iff s < lim(t)
@@ -1295,12 +1297,14 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
         j = __builtin_amdgcn_readfirstlane(j);   // the same block for every lane: scalar base address
         char* stage = smem + buf * L::STAGE;
         const char* kp = reinterpret_cast<const char*>(a.k + ((size_t)bh * a.N + (size_t)j * kBlockK) * D);
-        const int nrows = a.N - j * kBlockK;
-        if (nrows >= kBlockK) {
+        if (j < a.kfull) {
 #pragma unroll
             for (int u = 0; u < KPW; ++u)
                 lds_copy16(kp, kofs(u), (lds_ptr_t)(stage + (wave * KPW + u) * 1024));
-        } else {
+            return;
+        }
+        const int nrows = min(a.N - j * kBlockK, kBlockK);
+        if (a.kaligned) {
 #pragma unroll
             for (int u = 0; u < KPW; ++u) {
                 int r, c;
@@ -1308,6 +1312,18 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
                 const uint32_t off = (uint32_t)(min(r, nrows - 1) * D + c * 8) * 2u;
                 lds_copy16(kp, off, (lds_ptr_t)(stage + (wave * KPW + u) * 1024));
             }
+        } else {   // keys that do not start on 16 bytes: through registers, a few at a time
+            int p = wave * KPW * 64 + lane;
+            asm volatile("" : "+v"(p));
+#pragma unroll 1
+            for (int u = 0; u < KPW; ++u, p += 64) {
+                int r, c;
+                L::ksrc(p, r, c);
+                s16x8 x;
+                __builtin_memcpy(&x, reinterpret_cast<const uint16_t*>(kp + (uint32_t)(min(r, nrows - 1) * D + c * 8) * 2u), 16);
+                *reinterpret_cast<s16x8*>(stage + 16 * p) = x;
+            }
+            __builtin_amdgcn_s_waitcnt(0);
         }
     };
     // ... and its transposed values into stage `buf`'s V region.
@@ -1962,7 +1978,7 @@ struct AttnArgsF32 {
     float scale, c_log2;
     int causal_g;
     int prox_n;               // proxies a row keeps in LDS: NKr under a causal mask with routing, else 0
-    int aligned;              // k, v and the pooled rows start on 16 bytes (direct copies to LDS)
+    int aligned;              // k and v start on 16 bytes, as the workspace does (direct copies to LDS)
     float beta;
 };
 
@@ -2708,6 +2724,8 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.snake = s.causal && (long long)s.BH * s.NQ <= 1536;
         a.per_x = a.snake ? (s.NQ + 7) / 8
                   : s.causal ? 2 * ((s.NQ + 15) / 16) : (s.NQ + (8 >> a.hlog) - 1) / (8 >> a.hlog);
+        a.kaligned = (reinterpret_cast<uintptr_t>(k) & 15) == 0;
+        a.kfull = a.kaligned ? s.N / kBlockK : 0;
         a.scale = scale;
         a.causal_g = s.causal;
         a.beta = beta;
@@ -2741,8 +2759,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.vbar = ws.vbar;
         a.tau = ws.tau;
         a.prox_n = f32_prox_n(s);
-        a.aligned = ((reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v) |
-                      reinterpret_cast<uintptr_t>(ws.kbar) | reinterpret_cast<uintptr_t>(ws.vbar)) & 15) == 0;
+        a.aligned = ((reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v)) & 15) == 0;
         a.out = static_cast<float*>(out);
         a.part = ws.part;
         a.part_ml = ws.part_ml;

@@ -155,3 +155,32 @@ def test_counts_of_one_query_block(dev, dtype, d, bq):
     counts = torch.full((1, 3), -1, dtype=torch.int32, device=dev)
     sb.forward(q, k, v, bq, 64, 0.0, "sparse", counts=counts, mask_out=mask)
     assert np.array_equal(counts.cpu().numpy(), sb.unpack_mask(mask.cpu().numpy().view(np.uint32), w.NK).sum(axis=(2, 3)))
+
+
+@pytest.mark.parametrize("mode,g,d,bq,off", [("dense", 0, 64, 64, 1), ("sparse", 0, 128, 128, 1), ("sparse", 0, 128, 64, 2),
+                                             ("sparse", 1, 64, 128, 1), ("sparse_no_correction", 100, 128, 64, 4)])
+def test_bf16_tensors_off_16_bytes(dev, mode, g, d, bq, off):
+    # views that start 2 bytes or more into an allocation: the same results as aligned tensors, bit for bit
+    w = small_workload("off", (601,), d, bq, H=2, seed=4)
+    aligned = [t.to(dev) for t in synth.make_qkv(w)]
+    moved = []
+    for t in aligned + [torch.empty_like(aligned[0])]:
+        moved.append(torch.empty(t.numel() + off, device=dev, dtype=t.dtype)[off:].view(t.shape))
+        moved[-1].copy_(t)
+        assert moved[-1].data_ptr() % 16 == 2 * off
+    out = moved.pop()
+    ref = sb.forward(*aligned, bq, 64, 0.5, mode, causal_granule=g)
+    sb.forward(*moved, bq, 64, 0.5, mode, causal_granule=g, out=out)
+    assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("dtype,off", [("bf16", 2), ("bf16", 8), ("f32", 4)])
+def test_workspace_off_16_bytes(dev, dtype, off):
+    w = small_workload("wsoff", (601,), 128, 64, dtype=dtype, H=2, seed=4)
+    q, k, v = (t.to(dev) for t in synth.make_qkv(w))
+    ref = sb.forward(q, k, v, 64, 64, 0.5, "sparse")
+    n = sb.workspace_bytes(1, 2, 601, 128, 64, 64, "sparse", sb.SOL_BF16 if dtype == "bf16" else sb.SOL_F32)
+    buf = torch.full((n + off + 4096,), 0x5A, dtype=torch.uint8, device=dev)
+    out = sb.forward(q, k, v, 64, 64, 0.5, "sparse", workspace=buf[off:off + n])
+    assert torch.equal(out, ref)
+    assert bool((buf[:off] == 0x5A).all()) and bool((buf[off + n:] == 0x5A).all()), "written outside the workspace"
