@@ -62,13 +62,13 @@ __global__ __launch_bounds__(256) void proxy_map_kernel(const float* __restrict_
     }
 }
 
-// The row's order-preserving keys; 0, below every key, past the row's end.
+// Order-preserving keys of the row's entries j0 + lane + 64 i; 0, below every key, past the row's end.
 template <int KPL>
-__device__ __forceinline__ void load_keys(const float* __restrict__ row, int NKr, uint32_t (&key)[KPL]) {
+__device__ __forceinline__ void load_keys(const float* __restrict__ row, int NKr, int j0, uint32_t (&key)[KPL]) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < KPL; ++i) {
-        const int j = lane + 64 * i;
+        const int j = j0 + lane + 64 * i;
         key[i] = j < NKr ? order_key(row[j]) : 0u;
     }
 }
@@ -84,18 +84,44 @@ __device__ __forceinline__ int bits_below(uint64_t m) {
 }
 
 // ---------------------------------------------------------------------------
-// Top-k of each row.  A wave per row, KPL keys a lane (64 KPL >= NKr).  The largest K with at least k keys >= K is
-// built bit by bit; keys above K are kept, and of the keys equal to K the lowest indices until k are kept.  The
-// search stops at a K with exactly k keys >= K.  3,072 rows of 512: 9 us, against 75 us with a
-// workgroup per row and a radix select in LDS whose digit scan ran on one thread.
+// Top-k of each row.  WPR waves per row (1, or all four of a workgroup), KPL keys a lane (64 KPL WPR >= NKr), wave w
+// holding the entries from 64 KPL w on.  The largest K with at least k keys >= K is built bit by bit; keys above
+// K are kept, and of the keys equal to K the lowest indices until k are kept.  The search stops at a K with
+// exactly k keys >= K.  3,072 rows of 512: 9 us, against 75 us with a workgroup per row and a radix select in
+// LDS whose digit scan ran on one thread.  Rows past TOPK_ROW4 entries take four waves: see launch_topk.
 // ---------------------------------------------------------------------------
-template <int KPL>
+template <int KPL, int WPR>
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ shat, uint32_t* __restrict__ mask,
                                                    long long rows, int NKr, int MW, int k) {
-    const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    static_assert(WPR == 1 || WPR == 4, "a wave or a workgroup per row");
+    __shared__ int part[2][4];
+    const int wave = threadIdx.x >> 6, j0 = WPR == 1 ? 0 : wave * 64 * KPL;
+    const long long r = (long long)blockIdx.x * (4 / WPR) + (WPR == 1 ? wave : 0);
     if (r >= rows) return;
     uint32_t key[KPL];
-    load_keys<KPL>(shat + r * NKr, NKr, key);
+    load_keys<KPL>(shat + r * NKr, NKr, j0, key);
+    // Sum over the row's waves; `before` receives the sum over the waves before this one.  The two sets of partial
+    // sums alternate, so one barrier per call is enough.
+    int turn = 0;
+    auto row_sum = [&](int v, int* before) __attribute__((always_inline)) -> int {
+        if constexpr (WPR == 1) {
+            if (before) *before = 0;
+            return v;
+        } else {
+            turn ^= 1;
+            if ((threadIdx.x & 63) == 0) part[turn][wave] = v;
+            __syncthreads();
+            int sum = 0, pre = 0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int x = part[turn][w];
+                if (w < wave) pre += x;
+                sum += x;
+            }
+            if (before) *before = __builtin_amdgcn_readfirstlane(pre);
+            return __builtin_amdgcn_readfirstlane(sum);   // the same in every wave: uniform control flow
+        }
+    };
     uint32_t kth = 0u;
     int above = -1;   // keys > kth, once known to be needed
     for (int bit = 31; bit >= 0; --bit) {
@@ -103,6 +129,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sha
         int cnt = 0;
 #pragma unroll
         for (int i = 0; i < KPL; ++i) cnt += __popcll(__ballot(key[i] >= cand));
+        cnt = row_sum(cnt, nullptr);
         if (cnt >= k) kth = cand;
         if (cnt == k) {
             above = 0;   // exactly k keys >= kth: every one equal to it is kept too
@@ -114,16 +141,23 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sha
         above = 0;
 #pragma unroll
         for (int i = 0; i < KPL; ++i) above += __popcll(__ballot(key[i] > kth));
-        take_eq = k - above;
+        take_eq = k - row_sum(above, nullptr);
     }
     uint32_t* words = mask + r * MW;
-    int seen = 0;
+    uint64_t eq[KPL];
+    int mine = 0;
 #pragma unroll
     for (int i = 0; i < KPL; ++i) {
-        const bool is_eq = key[i] == kth && (int)(threadIdx.x & 63) + 64 * i < NKr;   // kth may be 0
-        const uint64_t eq = __ballot(is_eq);
-        store_words(words, MW, i, __ballot(key[i] > kth || (is_eq && seen + bits_below(eq) < take_eq)));
-        seen += __popcll(eq);
+        eq[i] = __ballot(key[i] == kth && j0 + (int)(threadIdx.x & 63) + 64 * i < NKr);   // kth may be 0
+        mine += __popcll(eq[i]);
+    }
+    int seen;
+    row_sum(mine, &seen);
+#pragma unroll
+    for (int i = 0; i < KPL; ++i) {
+        const bool is_eq = (eq[i] >> (threadIdx.x & 63)) & 1u;
+        store_words(words, MW, j0 / 64 + i, __ballot(key[i] > kth || (is_eq && seen + bits_below(eq[i]) < take_eq)));
+        seen += __popcll(eq[i]);
     }
 }
 
@@ -157,7 +191,7 @@ __global__ __launch_bounds__(256) void topp_kernel(const float* __restrict__ sha
     const float* row = shat + r * NKr;
     const int lane = threadIdx.x & 63;
     uint32_t key[KPL];
-    load_keys<KPL>(row, NKr, key);
+    load_keys<KPL>(row, NKr, 0, key);
     uint32_t kmax = 0u;
 #pragma unroll
     for (int i = 0; i < KPL; ++i) kmax = max(kmax, key[i]);
@@ -203,13 +237,20 @@ __global__ __launch_bounds__(256) void topp_kernel(const float* __restrict__ sha
     }
 }
 
-// Keys per lane: the smallest power of two (at least 4) that covers the row.
+// Keys per lane: the smallest power of two (at least 4) that covers the row.  Top-k rows of more than TOPK_ROW4
+// entries are dealt to four waves.
+constexpr int TOPK_ROW4 = 2048;
 template <int KPL>
 void launch_topk(const float* shat, uint32_t* mask, long long rows, int NKr, int MW, int k, hipStream_t st) {
-    if constexpr (KPL < 128) {
+    if constexpr (KPL < 32) {
         if (NKr > 64 * KPL) return launch_topk<2 * KPL>(shat, mask, rows, NKr, MW, k, st);
     }
-    topk_kernel<KPL><<<dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st>>>(shat, mask, rows, NKr, MW, k);
+    if (NKr > TOPK_ROW4) {
+        if (NKr <= 4096) topk_kernel<16, 4><<<dim3((unsigned)rows), dim3(256), 0, st>>>(shat, mask, rows, NKr, MW, k);
+        else topk_kernel<32, 4><<<dim3((unsigned)rows), dim3(256), 0, st>>>(shat, mask, rows, NKr, MW, k);
+        return;
+    }
+    topk_kernel<KPL, 1><<<dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st>>>(shat, mask, rows, NKr, MW, k);
 }
 template <int KPL>
 void launch_topp(const float* shat, uint32_t* mask, long long rows, int NKr, int MW, float p, hipStream_t st) {
