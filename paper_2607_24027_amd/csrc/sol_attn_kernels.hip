@@ -1855,7 +1855,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
 // sparse modes), so the workgroups resident on one XCD work through neighbouring blocks of one
 // head and share its K/V in their L2.  Under a causal mask the work of a query block grows with its index, so the
 // head's blocks are cut into 16 segments and queue x takes segment 15 - x (descending, the
-// longer blocks first) and then segment x, head by head; short heads (AttnArgs::snake) are instead dealt to the
+// longer blocks first) and then segment x, head by head; some launches (AttnArgs::snake) instead deal them to the
 // queues block by block, to and fro, the longest blocks of all heads first: 16 segments of a few blocks
 // do not come out even, and a long block that starts late ends late.  Consecutive workgroups go round-robin to the 8
 // XCDs, so workgroup w serves queue w & 7 first; once that queue is empty it takes blocks
@@ -2667,6 +2667,22 @@ uint32_t dense_count(const Shape& s) {
     return tot;
 }
 
+// Whether a causal launch deals its query blocks to the queues block by block (AttnArgs::snake) instead of head by head:
+// where the end of the launch counts for more than one XCD staying with one head.  Measured over 300 shapes
+// (d, block_q, mode, granule), time head by head / block by block:
+//   2 to 16 heads, 128 to 1,536 blocks   0.97 to 1.30, mean 1.07 (16 heads x 33 blocks, dense, d = 64: 84 / 79 us;
+//                                        12 x 64, dense, d = 128: 1.14; 2 x 591 3,190 / 2,550)
+//   more heads                           0.86 to 1.27: many short heads at once do not fit an XCD's L2
+//                                        (32 x 16 blocks, dense, d = 128: 0.89 to 0.95)
+//   one head                             0.86 to 1.05: one round, in which the segments pair long blocks with short
+//   fewer than 128 blocks                0.94 to 1.09, mean 1.00
+//   more than 1,536                      0.91 to 0.96 (24 x 146 2,070 / 2,157, 24 x 256 5,940 / 6,510)
+//   key-split kernel (64-row blocks, d = 128), which reads twice the tiles per query row: 0.69 to 1.17, mean 0.97
+bool causal_snake(const Shape& s) {
+    const long long blocks = (long long)s.BH * s.NQ;
+    return s.causal && !(s.d == 128 && s.bq == 64) && s.BH >= 2 && s.BH <= 16 && blocks >= 128 && blocks <= 1536;
+}
+
 hipError_t launch_forward(const Shape& s, const void* q, const void* k, const void* v, void* out, float beta,
                           const Workspace& ws, uint32_t* counts, uint32_t* mask_out, hipStream_t st,
                           hipEvent_t ev_start, hipEvent_t ev_stop) {
@@ -2717,11 +2733,7 @@ hipError_t launch_forward(const Shape& s, const void* q, const void* k, const vo
         a.mask_out = mask_out;
         a.BH = s.BH; a.N = s.N; a.NQ = s.NQ; a.NK = s.NK; a.NKr = s.NKr; a.NC = s.NC; a.MW = s.MW;
         a.hlog = s.causal ? 0 : heads_in_flight_log2(s);
-        // Causal launches of at most three rounds of two workgroups a CU: the end of the launch counts for more than one
-        // XCD staying with one head.  Measured, block by block against head by head: 16 heads x 33 blocks (dense)
-        // 84 -> 79 us at d = 64, 125 -> 109 at d = 128; 12 x 110 (dense) 674 -> 604; 4 x 256 1,120 -> 997; 2 x 591
-        // 3,190 -> 2,550; but 24 x 146 2,070 -> 2,157, 24 x 256 5,940 -> 6,510.
-        a.snake = s.causal && (long long)s.BH * s.NQ <= 1536;
+        a.snake = causal_snake(s);
         a.per_x = a.snake ? (s.NQ + 7) / 8
                   : s.causal ? 2 * ((s.NQ + 15) / 16) : (s.NQ + (8 >> a.hlog) - 1) / (8 >> a.hlog);
         a.kaligned = (reinterpret_cast<uintptr_t>(k) & 15) == 0;
