@@ -190,3 +190,15 @@ def test_workspace_off_16_bytes(dev, dtype, off):
     out = sb.forward(q, k, v, 64, 64, 0.5, "sparse", workspace=buf[off:off + n])
     assert torch.equal(out, ref)
     assert bool((buf[:off] == 0x5A).all()) and bool((buf[off + n:] == 0x5A).all()), "written outside the workspace"
+
+
+def test_pooling_of_inputs_past_one_launch(dev):
+    # 1.1 GB of inputs: a launch per tensor; the same means as of a slice small enough for one launch, bit for bit
+    g = torch.Generator(device=dev).manual_seed(3)
+    q, k, v = (torch.randn(1, 24, 60001, 128, generator=g, device=dev).bfloat16() for _ in range(3))
+    assert 3 * q.numel() * 2 > 1 << 30
+    got = sb.pool_blocks(q, k, v, 128, 64)
+    for h in (0, 23):
+        part = sb.pool_blocks(*(x[:, h:h + 1].contiguous() for x in (q, k, v)), 128, 64)
+        for a, b in zip(got, part):
+            assert torch.equal(a[:, h:h + 1], b)
