@@ -1678,9 +1678,15 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
                 // lowest outside the tile loops (routing, epilogue), which the other workgroup on the
                 // CU can then overlap: 1-2.4% faster in the sparse modes, dense within noise.  Under
                 // the key split (8 + 8 slots) the PV half goes first instead: 1.5% faster there.
+                // Dense blocks of 64 rows at d = 64 keep one priority: they are all alike, and the phases' priorities
+                // hold the two waves of a SIMD in step, so that a round of blocks ends all at once and a
+                // part of a round takes as long as a whole one (8,192 tokens, us, in step / one priority:
+                // 9 heads 261 / 236, 12 heads 286 / 261, 17 heads 374 / 353; 4 heads 123 / 135, 8 heads 176 / 178,
+                // 24 heads 474 / 483; the same work in source order 240, 268, 359, 139, 180, 493).
+                constexpr bool kPhases = !(D == 64 && BQ == 64 && MODE == kDense && !CAUSAL);
                 constexpr int kPrioQK = NS == 1 ? 1 : 2, kPrioPV = NS == 1 ? 2 : 1;
-                if (sl == 0) __builtin_amdgcn_s_setprio(kPrioQK);
-                if (sl == NQK) __builtin_amdgcn_s_setprio(kPrioPV);
+                if (sl == 0 && kPhases) __builtin_amdgcn_s_setprio(kPrioQK);
+                if (sl == NQK && kPhases) __builtin_amdgcn_s_setprio(kPrioPV);
                 prefetch(sl + 2);
                 const int id = index(sl);
                 if (kind(sl) == 0) {
