@@ -1106,11 +1106,16 @@ template <int D, int BQ>
 constexpr int kAttnThreads = kAttnKeySplit<D, BQ> ? 256 : BQ * 2;
 
 // Waves per SIMD that the registers are budgeted for.  d = 64 with 128-row blocks: three (168 registers; a tile has half
-// the MFMAs for the same softmax work, so a third wave has more to fill: 24 heads of 10,865 tokens sparse 313 -> 289 us,
-// with four and their spills 296); with 64-row blocks (two waves a workgroup) LDS holds four workgroups a CU, two
-// waves.
-template <int D, int BQ>
-constexpr int kAttnWaves = D == 64 && BQ == 128 ? 3 : 2;
+// the MFMAs for the same softmax work, so a third wave has more to fill).  24 heads of 10,865 tokens, us, with two /
+// three / four waves: dense 755 / 724 / 882, sparse 258 / 253 / 345, without correction 239 / 236 / 313; four spill in
+// every tile, three 36 bytes a lane outside the tile loop (sparse mode).
+// Causal kernels of that shape need up to 195 registers: with three waves they spill 20 to 56 bytes, the
+// sparse one in its tile loop.  Two waves are faster in dense mode (40 heads of 8,000 tokens 397 against 409) and, in
+// the routing modes, up to kTwoWaveBlocks query blocks: 528 blocks 45.4 / 47.8, 1,008 78.1 / 81.6, 1,200 to 1,280 0 to
+// 5 % faster, 1,500 to 2,016 within 3 % either way, 2,520 169 / 164.
+// With 64-row blocks (two waves a workgroup) LDS holds four workgroups a CU, two waves.
+constexpr bool kThirdWave(int d, int bq, int mode, bool causal) { return d == 64 && bq == 128 && !(causal && mode == kDense); }
+constexpr int kTwoWaveBlocks = 1280;
 // One query block (b, h, qi) of the fused kernel; y is its position in its XCD's queue.
 template <int D, int BQ, int MODE, bool CAUSAL>
 __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const int bh, const int qi, const int y) {
@@ -1869,8 +1874,8 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
 // thus get help at the end instead of finishing last.  A block's result does not depend on
 // which workgroup computes it, and every claim either takes a block or finds a queue empty
 // for good, so each workgroup stops after at most eight failed claims.
-template <int D, int BQ, int MODE, bool CAUSAL>
-__global__ __launch_bounds__((kAttnThreads<D, BQ>)) __attribute__((amdgpu_waves_per_eu(kAttnWaves<D, BQ>, kAttnWaves<D, BQ>)))
+template <int D, int BQ, int MODE, bool CAUSAL, int WAVES>
+__global__ __launch_bounds__((kAttnThreads<D, BQ>)) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 void routed_attn_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ int s_task[2];
@@ -2374,13 +2379,10 @@ hipError_t allow_lds(K kernel, size_t bytes) {
 int f32_prox_n(const Shape& s) { return s.causal && s.mode != kDense ? s.NKr : 0; }
 size_t f32_lds_bytes(const Shape& s) { return LdsF32(s.d, s.MW, s.NC, s.NK, f32_prox_n(s)).bytes; }
 
-template <int D, int BQ, int MODE, bool CAUSAL>
-hipError_t launch_attn_bf16(const Shape& s, const AttnArgs& a, hipStream_t st) {
-    size_t lds = attn_lds_bytes(s);
-    // Few causal blocks (at most four a CU): two workgroups a CU although three fit.  With three, the CUs that get
-    // three long blocks finish last (16 heads of 4,097 tokens, d = 64, dense: 111 against 83 us).
-    if (CAUSAL && kAttnWaves<D, BQ> > 2 && (long long)a.BH * a.NQ <= 1024) lds = std::max(lds, (size_t)kMaxLds / 3 + 1024);
-    auto kern = routed_attn_kernel<D, BQ, MODE, CAUSAL>;
+template <int D, int BQ, int MODE, bool CAUSAL, int WAVES>
+hipError_t launch_attn_bf16_waves(const Shape& s, const AttnArgs& a, hipStream_t st) {
+    const size_t lds = attn_lds_bytes(s);
+    auto kern = routed_attn_kernel<D, BQ, MODE, CAUSAL, WAVES>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     // persistent grid: as many workgroups as fit at once, a multiple of 8 (one share per XCD),
@@ -2397,6 +2399,18 @@ hipError_t launch_attn_bf16(const Shape& s, const AttnArgs& a, hipStream_t st) {
     b.resident = (int)(grid / 8);
     kern<<<dim3((unsigned)grid), dim3(kAttnThreads<D, BQ>), lds, st>>>(b);
     return hipGetLastError();
+}
+
+template <int D, int BQ, int MODE, bool CAUSAL>
+hipError_t launch_attn_bf16(const Shape& s, const AttnArgs& a, hipStream_t st) {
+    if constexpr (kThirdWave(D, BQ, MODE, CAUSAL)) {
+        if constexpr (CAUSAL) {
+            if ((long long)a.BH * a.NQ <= kTwoWaveBlocks) return launch_attn_bf16_waves<D, BQ, MODE, CAUSAL, 2>(s, a, st);
+        }
+        return launch_attn_bf16_waves<D, BQ, MODE, CAUSAL, 3>(s, a, st);
+    } else {
+        return launch_attn_bf16_waves<D, BQ, MODE, CAUSAL, 2>(s, a, st);
+    }
 }
 
 template <int D, int BQ, int MODE, bool CAUSAL>

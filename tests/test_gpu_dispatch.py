@@ -94,8 +94,10 @@ def test_forward_selects_by_the_threshold_entry_points_tau(dev, dtype, d, bq):
     (3, 9 * 64 + 1, 128, 64, 1, "sparse"),        # 10 blocks a head, not a multiple of 8
     (96, 1024, 64, 64, 130, "sparse"),            # many heads: head by head
     (97, 1023, 64, 64, 130, "sparse"),
-    (5, 2049, 64, 128, 1, "dense"),               # 128-row blocks at d = 64, two workgroups a CU
-    (121, 1089, 64, 128, 64, "sparse_no_correction"),   # 1,089 of them: three
+    (5, 2049, 64, 128, 1, "dense"),               # 128-row blocks at d = 64, two waves a SIMD
+    (121, 1089, 64, 128, 64, "sparse_no_correction"),   # 1,089 of them: two
+    (160, 1023, 64, 128, 1, "sparse"),            # 1,280: two
+    (183, 895, 64, 128, 1, "sparse"),             # 1,281: three
     (16, 6144, 64, 64, 130, "sparse"),            # 16 heads, 1,536 blocks: block by block
     (16, 6145, 64, 64, 130, "sparse_no_correction"),    # 1,552: head by head
     (15, 9 * 128, 128, 128, 1, "sparse"),         # 135 blocks, 9 a head: block by block, the last round is one block
