@@ -5,9 +5,9 @@
  *
  * All tensors are caller-owned, contiguous, row-major device buffers of shape
  * [B, H, N, d] (row stride d) unless stated otherwise, aligned to their element
- * type (k, and in f32 v, are read faster when they start on 16 bytes).  Every entry point
- * validates its arguments on the host and returns a negative error code before
- * any GPU call when they are invalid; sol_attn_last_error() then describes the
+ * type (k, and in f32 v, are read faster when they start on 16 bytes).  Every
+ * entry point validates its arguments on the host and returns a negative error
+ * code before any GPU call when they are invalid; sol_attn_last_error() then describes the
  * problem.  Compute calls are asynchronous on the given HIP stream (a
  * hipStream_t passed as void*; NULL means the default stream) and do not
  * synchronise it.  GPU faults surface as SOL_ERR_HIP from a later synchronising
@@ -16,13 +16,14 @@
  * Supported shapes: d in {64, 128}; block_k = 64; block_q in {64, 128};
  * N >= 1 with ragged last blocks (a block's statistics use only its valid
  * tokens); bf16 inputs (the hot path) and f32 inputs (f32 products
- * and sums throughout, on the f32 matrix instructions).  The per-block routing lists live on chip, which bounds N: bf16 at
+ * and sums throughout, on the f32 matrix instructions; moments summed in f64 in
+ * both).  The per-block routing lists live on chip, which bounds N: bf16 at
  * d = 128 up to 1,478,656 tokens (1,048,576 with a causal mask), at d = 64 up
  * to 1,971,200 (1,015,808 causal); beyond that the forward returns
  * SOL_ERR_UNSUPPORTED.  Two workgroups share a compute unit up to 245,760
  * tokens at d = 128 (causal too) and 737,280 at d = 64 (524,288 causal);
- * longer sequences run with one and take roughly twice as long per tile.  The softmax scale is 1/sqrt(d) for the exact logits and the
- * proxies alike.
+ * longer sequences run with one and take roughly twice as long per tile.  The
+ * softmax scale is 1/sqrt(d) for the exact logits and the proxies alike.
  *
  * Range contract of the bf16 path (checked by nobody: outside it results are
  * undefined, typically inf/NaN, and no error code is returned):
@@ -181,11 +182,13 @@ int sol_attn_forward(const void* q, const void* k, const void* v, void* out,
  * stream: hipStream_t or NULL.
  *
  * Selection is computed on chip from f32 pooled proxies s*Qbar_i.Kbar_j and
- * never written to memory unless mask_out is given.  In the sparse modes the
- * library also orders the query blocks of each head by their pooled queries, so
- * that blocks with similar selections run together and share L2, and starts a
- * block's walk over its selected key blocks at a phase set by its place in that
- * schedule.  Neither changes which blocks are selected; the start phase changes
+ * never written to memory unless mask_out is given; tau_i is the one that
+ * sol_attn_thresholds returns for the same pooled inputs, at every size (causal
+ * masks: see below).  In the bf16 sparse modes without a causal mask the library
+ * also orders the query blocks of each head (up to 4,096 of them) by their pooled
+ * queries, so that blocks with similar selections run together and share L2; bf16
+ * calls start a block's walk over its selected key blocks at a phase set by its
+ * place in the schedule.  Neither changes which blocks are selected; the start phase changes
  * the order in which a block's exact tiles are accumulated, so results differ
  * from an increasing-order walk by rounding only.  Both are functions of the
  * inputs, so results are deterministic, and with every block selected the walk

@@ -555,8 +555,8 @@ __global__ __launch_bounds__(256) void tau_kernel(const float* __restrict__ qbar
 
 // One lane's value moved over the wave by the VALU's data-parallel primitives (rows of 16 lanes); lanes without a source
 // or outside ROWS get 0.  A shuffle through the LDS crossbar takes 50 to 100 cycles, and the reductions and
-// scans of the routing prologue were chains of six (short calls 25.7 -> 25.3 us, f32 31.4 -> 30.8, image shape -0.3 %,
-// d = 64 and frame-causal layers -0.5 %, with the mean's sum taken while the proxies are formed).
+// scans of the routing prologue were chains of six (frame-causal layer 285.8 -> 284.0 us, with the mean's sum taken
+// while the proxies are formed).
 template <int CTRL, int ROWS = 0xF>
 __device__ __forceinline__ int dpp0(int x) {
     return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true);
@@ -1621,8 +1621,9 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, char* smem, const 
         // with PV(t)).  Successive MFMAs on one accumulator are at least two slots apart, and
         // operands are read from LDS two slots ahead.  Under the key split the same schedule has
         // 8 + 8 slots (one 32-key score tile, two P blocks), and at d = 64 8 + 8 slots with two
-        // pairs of exponentials beside each QK^T MFMA (4-5 % faster there than the same work in
-        // source order: sparse 289 -> 275, dense 802 -> 747 us at 24 heads of 10,865 tokens).
+        // pairs of exponentials beside each QK^T MFMA (3-6 % faster there than the same work in
+        // source order: 24 heads of 10,865 tokens, 128-row blocks, dense 770 -> 726 us, sparse 264 -> 256,
+        // without correction 251 -> 238).
         auto step = [&](auto par_tag, int t) SOL_INLINE {
             constexpr int P = decltype(par_tag)::value;
             constexpr int KOFF = (P ^ 1) * L::STAGE;   // K of tile t+1
@@ -1964,9 +1965,12 @@ void routed_attn_kernel(AttnArgs a) {
 // halves' softmax states merged at the end through LDS.
 // A block's tiles (correction tiles, then exact ones) may be dealt in turn to several workgroups, each of
 // which then writes its unnormalised O and (m, l) for finish_kernel to merge: see f32_units.
-// Measured (whole forward): 8 heads of 4,255 tokens, d = 128, sparse, 22 % kept: 5,560 -> 273 us against one thread
-// per query row on the VALU; 2 heads of 2,048, d = 64: 790 -> 31 us; dense, 32 heads of 4,096, d = 128: 135 TFLOP/s
-// (a large f32 matrix product reaches 154 on the same card).
+// Measured (whole forward): 8 heads of 4,255 tokens, d = 128, sparse, 22 % kept: 5,560 -> 290 us against one thread
+// per query row on the VALU; 2 heads of 2,048, d = 64: 790 -> 42 us; dense, 32 heads of 4,096, d = 128: 135 TFLOP/s
+// (a large f32 matrix product reaches 154 on the same card).  The exponentials are the hardware's (v_exp_f32, about
+// one unit in the last place) of log2-scaled scores.  The causal kernels' value-by-value tile costs registers that
+// the d = 128 ones do not have: they spill 256 to 404 bytes a lane (8 heads of 4,255, dense: 454 us causal, 659 without
+// a mask).
 // ---------------------------------------------------------------------------
 
 struct AttnArgsF32 {
@@ -2498,9 +2502,9 @@ size_t attn_lds_bytes(const Shape& s) {
 
 // How many workgroups share a query block of the f32 kernel.  The chip holds 512 of them, two a CU; a block
 // costs what its tiles cost, whose number only the routing knows.  Measured (us, this rule against whole
-// blocks): 64 blocks of 64 rows, d = 64, sparse (2 heads, 2,048 tokens) 31 against 53; 24 dense blocks (2 heads,
-// 1,500 tokens, d = 128) 52 against 206; 272 sparse blocks (8 heads, 4,255 tokens, d = 128) 272 against 401,
-// 1,632 of them (48 heads) 1,286 against 1,392.
+// blocks): 64 blocks of 64 rows, d = 64, sparse (2 heads, 2,048 tokens) 39 against 54; 24 dense blocks (2 heads,
+// 1,500 tokens, d = 128) 52 against 210; 272 sparse blocks (8 heads, 4,255 tokens, d = 128) 242 against 346,
+// 480 (8 heads, 7,680) 599 against 627 (dense 1,921 against 1,904), 1,632 (48 heads, 4,255) 958 against 990.
 //   fewer than 128 blocks   as many shares as give every CU one, up to 8; twice that under a causal mask,
 //                           where a block's tiles grow with its index
 //   fewer than 512          two shares for the first three quarters, six for the rest: the small shares fill

@@ -7,14 +7,15 @@ resident in HBM):
   pool        block means Q̄, K̄, V̄ of q, k, v (common to every routing scheme)
   thresholds  pooled-key moments and tau_i = mu_i + beta*sigma_i (Eq. threshold_stats_exact):
               the only routing work outside the fused attention kernel.  Its entry point
-              allocates and synchronises, so its kernels are timed by rocprofv3 only
-              (moments_partial_block, moments_final_kernel, tau_kernel); it is called here so
+              synchronises, so its kernels are timed by rocprofv3 only
+              (moments_partial_kernel, moments_final_kernel, tau_kernel); it is called here so
               that they appear in the trace.
   fused_route the fused kernel in sparse_no_correction mode at beta = +inf: every key block is
               routed and listed on chip, no tile is computed.  An upper bound of the in-kernel
               routing cost, since it also reads Q and writes O.
-  topk, topp  proxy map s_hat = s Q̄ K̄^T written to HBM, then a top-k (radix select) or top-p
-              (sort + cumulative mass) pass over every row, producing a key-block mask.
+  topk, topp  proxy map s_hat = s Q̄ K̄^T written to HBM, then a top-k (bitwise search for the
+              k-th largest key) or top-p (the same search by the mass above a key) pass over
+              every row, producing a key-block mask.
 
 k and p are chosen for about 15 % kept (the figure's operating density is not stated in the
 paper; Fig. density_distribution compares the schemes at 15 %).  One JSON line on stdout.
