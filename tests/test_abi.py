@@ -118,6 +118,13 @@ def test_longest_f32_sequences(d, bq, blocks, causal_blocks):
     assert call(*FAKE, 1, 1, 64 * causal_blocks + 1, d, bq, 64, 0.5, 1, f32, 1, *tiny) == sb.SOL_ERR_UNSUPPORTED
 
 
+def test_workspace_bytes_of_valid_f32_calls_are_not_zero():
+    # 0 means invalid or unsupported; dense f32 calls need no buffers of their own where no query block is shared
+    for n in (1, 64, 7680, 7872, 100000):
+        for mode in ("dense", "sparse"):
+            assert sb.workspace_bytes(1, 8, n, 128, 128, 64, mode, sb.SOL_F32) > 0
+
+
 def test_other_entry_points_validate():
     lib = sb.lib()
     assert lib.sol_attn_forward(None, None, None, None, 1, 1, 64, 64, 64, 64, 0.0, 1) == sb.SOL_ERR_INVALID_ARG
