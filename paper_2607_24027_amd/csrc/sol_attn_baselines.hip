@@ -144,20 +144,20 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sha
         take_eq = k - row_sum(above, nullptr);
     }
     uint32_t* words = mask + r * MW;
-    uint64_t eq[KPL];
-    int mine = 0;
+    // Should kth be 0, the padding's keys equal it too, but they come last and take_eq entries of the row do before them.
+    int seen = 0;
+    if constexpr (WPR > 1) {
+        int mine = 0;
 #pragma unroll
-    for (int i = 0; i < KPL; ++i) {
-        eq[i] = __ballot(key[i] == kth && j0 + (int)(threadIdx.x & 63) + 64 * i < NKr);   // kth may be 0
-        mine += __popcll(eq[i]);
+        for (int i = 0; i < KPL; ++i) mine += __popcll(__ballot(key[i] == kth));
+        row_sum(mine, &seen);
     }
-    int seen;
-    row_sum(mine, &seen);
 #pragma unroll
     for (int i = 0; i < KPL; ++i) {
-        const bool is_eq = (eq[i] >> (threadIdx.x & 63)) & 1u;
-        store_words(words, MW, j0 / 64 + i, __ballot(key[i] > kth || (is_eq && seen + bits_below(eq[i]) < take_eq)));
-        seen += __popcll(eq[i]);
+        const bool is_eq = key[i] == kth;
+        const uint64_t eq = __ballot(is_eq);
+        store_words(words, MW, j0 / 64 + i, __ballot(key[i] > kth || (is_eq && seen + bits_below(eq) < take_eq)));
+        seen += __popcll(eq);
     }
 }
 
