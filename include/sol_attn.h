@@ -184,7 +184,8 @@ int sol_attn_forward(const void* q, const void* k, const void* v, void* out,
  * Selection is computed on chip from f32 pooled proxies s*Qbar_i.Kbar_j and
  * never written to memory unless mask_out is given; tau_i is the one that
  * sol_attn_thresholds returns for the same pooled inputs, at every size (causal
- * masks: see below).  In the bf16 sparse modes without a causal mask the library
+ * masks: see below).  A single routable block, which is its own mean, is selected
+ * by tau = -INFINITY only.  In the bf16 sparse modes without a causal mask the library
  * also orders the query blocks of each head (up to 4,096 of them) by their pooled
  * queries, so that blocks with similar selections run together and share L2; bf16
  * calls start a block's walk over its selected key blocks at a phase set by its

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <string>
@@ -383,6 +384,10 @@ int forward_impl(const void* q, const void* k, const void* v, void* out, int B, 
         ev1 = g_timing.stop[g_timing.used];
         ++g_timing.used;
     }
+    // A single routable block is its own mean (sigma = 0): no finite cutoff selects it, whichever way the rounding of its
+    // proxy and of mu falls.  (A causal row with one routable block takes mu from that very proxy.)
+    if (!s.causal && s.NKr == 1 && tau > -std::numeric_limits<float>::infinity())
+        tau = std::numeric_limits<float>::infinity();
     e = sol::launch_forward(s, q, k, v, out, tau, ws, counts, mask_out, st, ev0, ev1);
     if (e != hipSuccess) return hip_fail(e, "forward launch");
     if (track_counts) {

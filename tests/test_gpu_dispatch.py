@@ -204,3 +204,17 @@ def test_pooling_of_inputs_past_one_launch(dev):
         part = sb.pool_blocks(*(x[:, h:h + 1].contiguous() for x in (q, k, v)), 128, 64)
         for a, b in zip(got, part):
             assert torch.equal(a[:, h:h + 1], b)
+
+
+@pytest.mark.parametrize("dtype,d,bq", [("bf16", 64, 64), ("bf16", 128, 128), ("f32", 64, 128), ("f32", 128, 64)])
+def test_a_single_routable_block_ties_with_its_mean(dev, dtype, d, bq):
+    # sigma = 0: the proxy equals mu, and selection is strict, whichever way their rounding falls; 64 heads so that
+    # rounding would select some.  Without a tail, with one forced block, and under a mask.
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(d + bq)
+    for n, keep, granule in ((1, 0, 0), (33, 0, 0), (64, 0, 0), (100, 64, 0), (50, 0, 50)):
+        q, k, v = (torch.randn(4, 16, n, d, generator=g).to(dt).to(dev) for _ in range(3))
+        for beta, want in ((0.0, 0), (0.7, 0), (-0.7, 0), (math.inf, 0), (-math.inf, 1)):
+            counts = torch.full((4, 16), -1, dtype=torch.int32, device=dev)
+            sb.forward(q, k, v, bq, 64, beta, "sparse", keep_tail_tokens=keep, counts=counts, causal_granule=granule)
+            assert bool((counts == want * -(-n // bq)).all()), (n, keep, granule, beta)
